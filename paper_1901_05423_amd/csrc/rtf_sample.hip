@@ -25,6 +25,19 @@ __device__ inline int32_t block_find_segment(const int64_t *off, int32_t D, int6
     return lo;
 }
 
+constexpr int SB_T = 1024;      // threads of the kernels that stage records
+constexpr int LCELLS = 1024;    // staged records, 64 KB: two blocks per CU
+constexpr int STAGE_MIN = 2;    // samples per cell that make staging pay
+
+// Bytes of guide table up to which single-distribution sampling fetches the
+// records by whole quads of lanes.  While the table fits the L2s the texture
+// path's 64 lines per wave load bound the kernel (2^26 samples with x from a
+// 1 MiB table: 798 us with a record per lane, 694 by quads; index only 658 and
+// 529); from about 16 MiB the lines from the fabric do, and the quads'
+// transposition only costs (256 MiB table: 1430 us a record per lane, 1440 by
+// quads; index only 1339 and 1351).
+constexpr int64_t QUAD_TABLE = 12 << 20;
+
 constexpr int SCHUNK = 256 * 8;  // samples per block step of the batched kernel
 constexpr int CHUNK_DISTS = 256;  // distributions a chunk can stage in LDS
 
@@ -57,11 +70,7 @@ __device__ inline Node load_node(const Node *nodes, int64_t j) {
     return r;
 }
 
-__device__ inline Cell load_cell(const Cell *cells, int64_t g) {
-    const uint4 *p = reinterpret_cast<const uint4 *>(cells + g);
-    uint4 v[CELL_WORDS];
-#pragma unroll
-    for (int w = 0; w < CELL_WORDS; ++w) v[w] = p[w];  // all in flight together
+__device__ inline Cell cell_of_words(const uint4 *v) {
     Cell r;
 #pragma unroll
     for (int w = 0; w < CELL_WORDS; ++w) {
@@ -71,6 +80,73 @@ __device__ inline Cell load_cell(const Cell *cells, int64_t g) {
     r.ref = (int32_t)v[CELL_WORDS - 1].z;
     r.aux = (int32_t)v[CELL_WORDS - 1].w;
     return r;
+}
+
+__device__ inline Cell load_cell(const Cell *cells, int64_t g) {
+    const uint4 *p = reinterpret_cast<const uint4 *>(cells + g);
+    uint4 v[CELL_WORDS];
+#pragma unroll
+    for (int w = 0; w < CELL_WORDS; ++w) v[w] = p[w];  // all in flight together
+    return cell_of_words(v);
+}
+
+// Record c of a staged table: word w of every record lies in a plane of its
+// own, [CELL_WORDS][LCELLS], so that a wave's 16-byte reads of one word
+// spread over all banks (in record order they would fall on a quarter).
+__device__ inline Cell lds_cell(const uint4 *s_cell, uint32_t c) {
+    uint4 v[CELL_WORDS];
+#pragma unroll
+    for (int w = 0; w < CELL_WORDS; ++w) v[w] = s_cell[w * LCELLS + c];
+    return cell_of_words(v);
+}
+
+// One 4x4 transposition step inside every quad of lanes: out0 takes a from
+// the lane itself where `odd` is clear and b from the partner lane (the DPP
+// quad permutation CTRL) where it is set; out1 the other way round.
+template <int CTRL>
+__device__ inline void quad_swap(uint32_t &a, uint32_t &b, bool odd) {
+    const uint32_t pa = (uint32_t)__builtin_amdgcn_mov_dpp((int)a, CTRL, 0xf, 0xf, true);
+    const uint32_t pb = (uint32_t)__builtin_amdgcn_mov_dpp((int)b, CTRL, 0xf, 0xf, true);
+    const uint32_t o0 = odd ? pb : a, o1 = odd ? b : pa;
+    a = o0;
+    b = o1;
+}
+template <int CTRL>
+__device__ inline void quad_swap4(uint4 &a, uint4 &b, bool odd) {
+    quad_swap<CTRL>(a.x, b.x, odd);
+    quad_swap<CTRL>(a.y, b.y, odd);
+    quad_swap<CTRL>(a.z, b.z, odd);
+    quad_swap<CTRL>(a.w, b.w, odd);
+}
+
+// Every lane's 64-byte record base[g], fetched by whole quads of lanes: in
+// step q the four lanes of a quad load the four 16-byte words of lane q's
+// record, so that a wave instruction touches 16 lines instead of 64, and a
+// 4x4 transposition inside the quads hands every lane its own words.  All
+// lanes of a quad must call it together.
+__device__ inline void load_record_quad(const void *base, uint32_t g, uint4 *v) {
+    static_assert(CELL_WORDS == 4 && sizeof(Dist) == 64, "one word of a record per lane of a quad");
+    const uint32_t lane = threadIdx.x;
+    const char *p = reinterpret_cast<const char *>(base) + 16 * (lane & 3);
+    const uint32_t g0 = (uint32_t)__builtin_amdgcn_mov_dpp((int)g, 0x00, 0xf, 0xf, true);
+    const uint32_t g1 = (uint32_t)__builtin_amdgcn_mov_dpp((int)g, 0x55, 0xf, 0xf, true);
+    const uint32_t g2 = (uint32_t)__builtin_amdgcn_mov_dpp((int)g, 0xaa, 0xf, 0xf, true);
+    const uint32_t g3 = (uint32_t)__builtin_amdgcn_mov_dpp((int)g, 0xff, 0xf, 0xf, true);
+    v[0] = *reinterpret_cast<const uint4 *>(p + ((uint64_t)g0 << 6));
+    v[1] = *reinterpret_cast<const uint4 *>(p + ((uint64_t)g1 << 6));
+    v[2] = *reinterpret_cast<const uint4 *>(p + ((uint64_t)g2 << 6));
+    v[3] = *reinterpret_cast<const uint4 *>(p + ((uint64_t)g3 << 6));
+    const bool o1 = lane & 1, o2 = lane & 2;
+    quad_swap4<0xb1>(v[0], v[1], o1);  // quad_perm 1 0 3 2
+    quad_swap4<0xb1>(v[2], v[3], o1);
+    quad_swap4<0x4e>(v[0], v[2], o2);  // quad_perm 2 3 0 1
+    quad_swap4<0x4e>(v[1], v[3], o2);
+}
+
+__device__ inline Cell load_cell_quad(const Cell *cells, uint32_t g) {
+    uint4 v[4];
+    load_record_quad(cells, g, v);
+    return cell_of_words(v);
 }
 
 // Marks every word of a record as used here, so that the record's loads,
@@ -86,19 +162,9 @@ __device__ inline void pin_cell(Cell &c) {
 // A sampled leaf with the keys of its interval's two ends (KEY_END for the
 // distribution's end); leaf -1 flags a damaged workspace.
 struct Hit {
-    int64_t i;
+    int32_t i;
     uint64_t lo, hi;
 };
-
-// Alg. 2: g = floor(xi * m); follow the reference until it names a leaf.
-// The cell record resolves the guide step and, for a cell that holds at most
-// CELL_BOUNDS lower bounds (or for u below the record's last key), the whole
-// sample: the leaf is a - 1 plus the number of the cell's lower bounds at or
-// below u.  Otherwise the descent continues from the cell's tree root.  A
-// reference outside the forest, or a path longer than the forest has nodes,
-// can only come from a damaged workspace.
-__device__ inline Hit resolve(const Node *nodes, const Wide *wide, const Cell &c, const Dist &P,
-                              uint64_t u, int64_t n_total);
 
 // floor(u m / 2^64) for distribution P's m cells, P the same for the whole
 // wave: a shift when m is a power of two (the shift is in the distribution's
@@ -110,13 +176,6 @@ __device__ inline int64_t cell_in(const Dist &P, uint64_t u) {
 
 __device__ inline int64_t cell_index(const Dist &P, uint64_t u) {
     return P.co + (int64_t)mulhi64(u, (uint64_t)P.m);
-}
-
-__device__ inline Hit descend(const Node *nodes, const Wide *wide, const Cell *cells, const Dist &P,
-                              uint64_t u, int64_t n_total) {
-    Cell c = load_cell(cells, cell_index(P, u));
-    pin_cell(c);
-    return resolve(nodes, wide, c, P, u, n_total);
 }
 
 __device__ inline Wide load_wide(const Wide *wide, int64_t j) {
@@ -133,115 +192,194 @@ __device__ inline Wide load_wide(const Wide *wide, int64_t j) {
     return r;
 }
 
-// The sample's leaf from its cell record c (and, past the record, the tree).
-// The record's own answer is computed for every kind of cell with selects
-// only (a covered cell is a record holding no bounds); only a descent
-// branches.
+// The three selections of a search, each under an execution mask instead of
+// with v_cndmask: a masked v_mov_b64 moves a whole key in one instruction
+// where a select takes two, and three or more selects on vcc in a row, which
+// is what the compiler makes of the plain code, issue at 23 cycles each here
+// instead of 4 (a compare between them, or the mask in another register
+// pair, restores the rate).
+
+// j = the number of k[1..5] at or below u before the first that is not, lo =
+// k[j], hi = k[j + 1].
+__device__ inline void count_bounds(const uint64_t *k, uint64_t u, int32_t &j, uint64_t &lo, uint64_t &hi) {
+    static_assert(CELL_BOUNDS == 5, "five compares");
+    uint64_t e, m2, m3, m4, m5;
+    j = 0;
+    lo = k[0];
+    hi = k[1];
+    asm("v_cmp_le_u64 vcc, %[k1], %[u]\n\t"
+        "v_cmp_le_u64 %[m2], %[k2], %[u]\n\t"
+        "v_cmp_le_u64 %[m3], %[k3], %[u]\n\t"
+        "v_cmp_le_u64 %[m4], %[k4], %[u]\n\t"
+        "v_cmp_le_u64 %[m5], %[k5], %[u]\n\t"
+        "s_and_saveexec_b64 %[e], vcc\n\t"
+        "v_mov_b64 %[lo], %[k1]\n\t"
+        "v_mov_b64 %[hi], %[k2]\n\t"
+        "v_mov_b32 %[j], 1\n\t"
+        "s_and_b64 exec, exec, %[m2]\n\t"
+        "v_mov_b64 %[lo], %[k2]\n\t"
+        "v_mov_b64 %[hi], %[k3]\n\t"
+        "v_mov_b32 %[j], 2\n\t"
+        "s_and_b64 exec, exec, %[m3]\n\t"
+        "v_mov_b64 %[lo], %[k3]\n\t"
+        "v_mov_b64 %[hi], %[k4]\n\t"
+        "v_mov_b32 %[j], 3\n\t"
+        "s_and_b64 exec, exec, %[m4]\n\t"
+        "v_mov_b64 %[lo], %[k4]\n\t"
+        "v_mov_b64 %[hi], %[k5]\n\t"
+        "v_mov_b32 %[j], 4\n\t"
+        "s_and_b64 exec, exec, %[m5]\n\t"
+        "v_mov_b64 %[lo], %[k5]\n\t"
+        "v_mov_b64 %[hi], %[k6]\n\t"
+        "v_mov_b32 %[j], 5\n\t"
+        "s_mov_b64 exec, %[e]"
+        : [e] "=&s"(e), [m2] "=&s"(m2), [m3] "=&s"(m3), [m4] "=&s"(m4), [m5] "=&s"(m5), [j] "+&v"(j),
+          [lo] "+&v"(lo), [hi] "+&v"(hi)
+        : [u] "v"(u), [k1] "v"(k[1]), [k2] "v"(k[2]), [k3] "v"(k[3]), [k4] "v"(k[4]), [k5] "v"(k[5]),
+          [k6] "v"(k[6])
+        : "vcc", "scc");
+}
+
+// One binary step past a node: u >= key goes right.  klo and khi keep the
+// last key at or below u and the last above it.
+__device__ inline void step_node(uint64_t key, int32_t c0, int32_t c1, uint64_t u, int32_t &jn,
+                                 uint64_t &klo, uint64_t &khi) {
+    uint64_t e;
+    jn = c0;
+    asm("v_cmp_le_u64 vcc, %[k], %[u]\n\t"
+        "s_and_saveexec_b64 %[e], vcc\n\t"
+        "v_mov_b64 %[klo], %[k]\n\t"
+        "v_mov_b32 %[jn], %[c1]\n\t"
+        "s_andn2_b64 exec, %[e], vcc\n\t"
+        "v_mov_b64 %[khi], %[k]\n\t"
+        "s_mov_b64 exec, %[e]"
+        : [e] "=&s"(e), [jn] "+&v"(jn), [klo] "+&v"(klo), [khi] "+&v"(khi)
+        : [u] "v"(u), [k] "v"(key), [c1] "v"(c1)
+        : "vcc", "scc");
+}
+
+// Two binary steps past a collapsed node.  A leaf child repeats its reference
+// (r[2s] == r[2s+1]) and ends the second step.
+__device__ inline void step_wide(const Wide &w, uint64_t u, int32_t &jn, uint64_t &klo, uint64_t &khi) {
+    uint64_t e, kc = w.kc[0];
+    int32_t g0 = w.r[0], g1 = w.r[1];
+    asm("v_cmp_le_u64 vcc, %[k], %[u]\n\t"
+        "s_and_saveexec_b64 %[e], vcc\n\t"
+        "v_mov_b64 %[klo], %[k]\n\t"
+        "v_mov_b64 %[kc], %[kc1]\n\t"
+        "v_mov_b32 %[g0], %[r2]\n\t"
+        "v_mov_b32 %[g1], %[r3]\n\t"
+        "s_andn2_b64 exec, %[e], vcc\n\t"
+        "v_mov_b64 %[khi], %[k]\n\t"
+        "s_mov_b64 exec, %[e]"
+        : [e] "=&s"(e), [klo] "+&v"(klo), [khi] "+&v"(khi), [kc] "+&v"(kc), [g0] "+&v"(g0), [g1] "+&v"(g1)
+        : [u] "v"(u), [k] "v"(w.k), [kc1] "v"(w.kc[1]), [r2] "v"(w.r[2]), [r3] "v"(w.r[3])
+        : "vcc", "scc");
+    if (g0 == g1) jn = g0;
+    else step_node(kc, g0, g1, u, jn, klo, khi);
+}
+
+// Alg. 2: g = floor(xi * m); follow the reference until it names a leaf.
+// The cell record c resolves the guide step and, for a cell that holds at
+// most CELL_BOUNDS lower bounds (or for u below the record's last key), the
+// whole sample: the leaf is a - 1 plus the number of the cell's lower bounds
+// at or below u.  Otherwise the descent continues from the cell's tree root.
+// A reference outside the forest, or a path longer than the forest has nodes,
+// can only come from a damaged workspace.
+//
+// The record's answer needs no look at how many bounds it holds: the key
+// after the last bound is the upper end of the cell's last interval, which
+// lies above u, so the count ends there and the unused slots (0) past it are
+// never reached; a covered cell counts none.  The one key that u can equal
+// without reaching it is KEY_END, at u = 2^64 - 1: there the count compares
+// 2^64 - 2, which every real key below KEY_END is at most (W <= 2^63).
 __device__ inline Hit resolve(const Node *nodes, const Wide *wide, const Cell &c, const Dist &P,
                               uint64_t u, int64_t n_total) {
-    const bool covered = c.ref < 0;  // one interval covers the cell
-    const int lim = covered ? 0 : (c.aux < 0 ? ~c.aux : CELL_BOUNDS);  // lower bounds held
-    int j = 0;
-    uint64_t lo = c.k[0], hi = c.k[1];
-#pragma unroll
-    for (int t = 1; t <= CELL_BOUNDS; ++t) {
-        const bool le = t <= lim && c.k[t] <= u;
-        j = le ? t : j;
-        lo = le ? c.k[t] : lo;
-        hi = le ? c.k[t + 1] : hi;
-    }
     Hit h;
-    h.i = covered ? ~(int64_t)c.ref : (int64_t)c.ref - 1 + j;
-    h.lo = lo;
-    h.hi = hi;
-    if (!covered && c.aux >= 0 && u >= c.k[CELL_KEYS - 1]) {  // past the record: the tree
+    int32_t j;
+    count_bounds(c.k, u - (u == ~0ull ? 1 : 0), j, h.lo, h.hi);
+    const int32_t sgn = c.ref >> 31;  // covered: leaf ~ref, else the leaf before a, plus j
+    h.i = (c.ref ^ sgn) + ~sgn + j;
+    if ((c.ref | c.aux) >= 0 && u >= c.k[CELL_KEYS - 1]) {  // past the record: the tree
         // Both bounds adjacent to the sampled leaf i are its ancestors when
         // they lie inside the cell, so the descent meets U_i as the last key
         // at or below u and U_{i+1} as the last key above it; only when i is
-        // the cell's last leaf is U_{i+1} read after the descent.
+        // the cell's last leaf (no key above u met: they are not 0) is
+        // U_{i+1} read after the descent.
+        const int32_t nt = (int32_t)n_total;
         uint64_t klo = c.k[CELL_KEYS - 1], khi = 0;
-        bool hi_seen = false;
-        int32_t jn = c.aux;
+        int32_t jn = c.aux, steps = 0;
         if (wide) {
             // collapsed nodes: two binary levels per record (Sec. 5)
-            for (int64_t steps = 0; jn >= 0; steps += 2) {
-                if (jn >= n_total || steps > n_total) {
-                    h.i = -1;
-                    return h;
-                }
-                const Wide wn = load_wide(wide, jn);
-                const bool right = u >= wn.k;
-                klo = right ? wn.k : klo;
-                khi = right ? khi : wn.k;
-                hi_seen = hi_seen || !right;
-                const int32_t g0 = right ? wn.r[2] : wn.r[0];
-                const int32_t g1 = right ? wn.r[3] : wn.r[1];
-                const uint64_t kc = right ? wn.kc[1] : wn.kc[0];
-                if (g0 == g1) {  // the child is a leaf
-                    jn = g0;
-                } else {
-                    const bool r2 = u >= kc;
-                    klo = r2 ? kc : klo;
-                    khi = r2 ? khi : kc;
-                    hi_seen = hi_seen || !r2;
-                    jn = r2 ? g1 : g0;
-                }
+            while (jn >= 0 && jn < nt && steps <= nt) {
+                step_wide(load_wide(wide, jn), u, jn, klo, khi);
+                ++steps;
             }
         } else {
-            for (int64_t steps = 0; jn >= 0; ++steps) {
-                if (jn >= n_total || steps > n_total) {
-                    h.i = -1;
-                    return h;
-                }
+            while (jn >= 0 && jn < nt && steps <= nt) {
                 const Node nd = load_node(nodes, jn);
-                const bool right = u >= nd.key;
-                klo = right ? nd.key : klo;
-                khi = right ? khi : nd.key;
-                hi_seen = hi_seen || !right;
-                jn = right ? nd.c1 : nd.c0;
+                step_node(nd.key, nd.c0, nd.c1, u, jn, klo, khi);
+                ++steps;
             }
         }
-        h.i = ~(int64_t)jn;
-        if (h.i < P.eo || h.i >= P.eo + P.n) {
-            h.i = -1;
-            return h;
-        }
+        h.i = jn < 0 ? ~jn : (int32_t)-1;
         h.lo = klo;
-        h.hi = hi_seen ? khi : ((h.i + 1 < P.eo + P.n) ? nodes[h.i + 1].key : KEY_END);
+        h.hi = khi;
+        if (khi == 0 && (uint32_t)(h.i - (int32_t)P.eo) < (uint32_t)P.n)
+            h.hi = (uint32_t)(h.i - (int32_t)P.eo) + 1 < (uint32_t)P.n ? nodes[(int64_t)h.i + 1].key : KEY_END;
     }
-    if (h.i < P.eo || h.i >= P.eo + P.n) h.i = -1;
+    if ((uint32_t)(h.i - (int32_t)P.eo) >= (uint32_t)P.n) h.i = -1;
     return h;
+}
+
+__device__ inline Hit descend(const Node *nodes, const Wide *wide, const Cell *cells, const Dist &P,
+                              uint64_t u, int64_t n_total) {
+    Cell c = load_cell(cells, cell_index(P, u));
+    pin_cell(c);
+    return resolve(nodes, wide, c, P, u, n_total);
 }
 
 // x = (i + ((t - C_i) + lo * 2^-64) / w_i) / n with t:lo = u * W, where
 // C_i = floor(U_i * W / 2^64) recovers the exact partial sum from a key.
 // For the sampled i, 0 <= t - C_i < w_i = C_{i+1} - C_i < 2^32 and
-// i - eo < 2^31, so those three convert to FP64 from 32 bits (one
-// instruction each, and the same values).  The division by n is a product
-// with 1/n, computed once where the distribution is the same for a whole
-// loop; the result is kept at most 1 (it could round one ulp above 1 when
-// the offset in the interval rounds up to w_i in the last leaf).
+// i - eo < 2^31, so those convert to FP64 from 32 bits (one instruction
+// each, and the same values).  The weight itself needs no second product:
+// (U_{i+1} - U_i) W / 2^64 differs from w_i by less than W 2^-63 (KEY_END
+// stands one below 2^64) and its FP64 value by 2^-20 more, so for W < 2^61
+// rounding it to an integer gives w_i exactly.  The division by n is a
+// product with 1/n, computed once where the distribution is the same for a
+// whole loop; the result is kept at most 1 (it could round one ulp above 1
+// when the offset in the interval rounds up to w_i in the last leaf).
 __device__ inline double position(const Dist &P, const Hit &h, uint64_t u) {
     const uint64_t W = P.W;
     const uint64_t Ci = mulhi64(h.lo, W);
-    const uint64_t Cn = (h.hi == KEY_END) ? W : mulhi64(h.hi, W);
     const uint64_t t = mulhi64(u, W);
     const uint64_t lo = u * W;
-    const double frac = div_small((double)(uint32_t)(t - Ci) + ldexp((double)lo, -64), (double)(uint32_t)(Cn - Ci));
-    const double x = ((double)(int32_t)(h.i - P.eo) + frac) * (1.0 / (double)P.n);
+    double w;
+    if (P.s >= 3) {  // W < 2^61
+        const uint64_t d = h.hi - h.lo;
+        w = __builtin_rint(__builtin_fma((double)(uint32_t)(d >> 32), 0x1p32, (double)(uint32_t)d) *
+                           (__builtin_fma((double)(uint32_t)(W >> 32), 0x1p32, (double)(uint32_t)W) * 0x1p-64));
+    } else {
+        const uint64_t Cn = (h.hi == KEY_END) ? W : mulhi64(h.hi, W);
+        w = (double)(uint32_t)(Cn - Ci);
+    }
+    const double lod = __builtin_fma((double)(uint32_t)(lo >> 32), 0x1p32, (double)(uint32_t)lo);
+    const double frac = div_small(__builtin_fma(lod, 0x1p-64, (double)(uint32_t)(t - Ci)), w);
+    const double x = ((double)(h.i - (int32_t)P.eo) + frac) * (1.0 / (double)P.n);
     return __builtin_fmin(x, 1.0);
 }
 
 // The same, for a leaf found without its keys (the baselines).
 __device__ inline double position_of(const Node *nodes, const Dist &P, int64_t i, uint64_t u) {
     Hit h;
-    h.i = i;
+    h.i = (int32_t)i;
     h.lo = nodes[i].key;
     h.hi = (i + 1 < P.eo + P.n) ? nodes[i + 1].key : KEY_END;
     return position(P, h, u);
 }
 
-template <bool BATCHED, bool WANT_X>
+template <bool BATCHED, bool WANT_X, bool QUAD>
 __global__ __launch_bounds__(256) void k_sample(const Node *__restrict__ nodes,
                                                 const Wide *__restrict__ wide,
                                                 const Cell *__restrict__ cells,
@@ -251,23 +389,33 @@ __global__ __launch_bounds__(256) void k_sample(const Node *__restrict__ nodes,
                                                 const uint64_t *__restrict__ u, int64_t S,
                                                 int32_t *__restrict__ idx,
                                                 double *__restrict__ x) {
-    auto one = [&](int64_t s, const Dist &P) {
-        const uint64_t us = __builtin_nontemporal_load(u + s);
-        Hit h;
-        h.i = -1;
-        if (!(P.flags & DIST_ZERO)) h = descend(nodes, wide, cells, P, us, n_total);
-        if (h.i < 0) {
-            idx[s] = -1;
-            if (WANT_X) x[s] = __builtin_nan("");
-            return;
-        }
-        __builtin_nontemporal_store((int32_t)(h.i - P.eo), idx + s);
-        if (WANT_X) __builtin_nontemporal_store(position(P, h, us), x + s);
-    };
     if (!BATCHED) {
+        const Dist P = dists[0];
         const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-        for (int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; s < S; s += stride)
-            one(s, dists[0]);
+        const bool zero = P.flags & DIST_ZERO;
+        int64_t s0 = (int64_t)blockIdx.x * blockDim.x;
+        if (s0 >= S) return;
+        auto at = [&](int64_t s) { return __builtin_nontemporal_load(u + (s < S ? s : S - 1)); };
+        uint64_t next = at(s0 + threadIdx.x);
+        for (; s0 < S; s0 += stride) {
+            const int64_t s = s0 + threadIdx.x;
+            const uint64_t us = next;
+            next = at(s + stride);
+            Hit h;
+            h.i = -1;
+            if (!zero) {
+                Cell c = QUAD ? load_cell_quad(cells, (uint32_t)cell_in(P, us)) : load_cell(cells, cell_in(P, us));
+                pin_cell(c);
+                h = resolve(nodes, wide, c, P, us, n_total);
+            }
+            if (s < S) {
+                __builtin_nontemporal_store(h.i < 0 ? (int32_t)-1 : h.i - (int32_t)P.eo, idx + s);
+                if (WANT_X) {
+                    const double px = position(P, h, us);
+                    __builtin_nontemporal_store(h.i < 0 ? (double)__builtin_nan("") : px, x + s);
+                }
+            }
+        }
         return;
     }
     __shared__ int64_t s_soff[256];
@@ -284,7 +432,7 @@ __global__ __launch_bounds__(256) void k_sample(const Node *__restrict__ nodes,
             if (WANT_X) x[s] = __builtin_nan("");
             return;
         }
-        __builtin_nontemporal_store((int32_t)(h.i - P.eo), idx + s);
+        __builtin_nontemporal_store(h.i - (int32_t)P.eo, idx + s);
         if (WANT_X) __builtin_nontemporal_store(position(P, h, us), x + s);
     };
     // two samples whose parameters are Pa and Pb, taken by value: through a
@@ -367,9 +515,6 @@ __global__ __launch_bounds__(256) void k_sample(const Node *__restrict__ nodes,
 // its cell record from LDS and only the rare descents reach L2.  Copying a
 // record streams 64 bytes, at most 32 per sample of the segment; a random L2
 // read per sample costs more.
-constexpr int SB_T = 1024;
-constexpr int LCELLS = 1024;    // 64 KB of records: two blocks per CU
-constexpr int STAGE_MIN = 2;
 template <bool WANT_X>
 __global__ __launch_bounds__(SB_T) __attribute__((amdgpu_waves_per_eu(8))) void k_sample_staged(
     const Node *__restrict__ nodes, const Wide *__restrict__ wide, const Cell *__restrict__ cells,
@@ -385,7 +530,7 @@ __global__ __launch_bounds__(SB_T) __attribute__((amdgpu_waves_per_eu(8))) void 
             if (WANT_X) x[s] = __builtin_nan("");
             return;
         }
-        __builtin_nontemporal_store((int32_t)(h.i - P.eo), idx + s);
+        __builtin_nontemporal_store(h.i - (int32_t)P.eo, idx + s);
         if (WANT_X) __builtin_nontemporal_store(position(P, h, us), x + s);
     };
     for (int64_t s0 = r0; s0 < r1;) {  // uniform loop over the share's segments
@@ -399,19 +544,19 @@ __global__ __launch_bounds__(SB_T) __attribute__((amdgpu_waves_per_eu(8))) void 
         const bool staged = !zero && P.m <= LCELLS && e - s0 >= STAGE_MIN * P.m;
         if (staged) {
             const uint4 *src = reinterpret_cast<const uint4 *>(cells + P.co);
-            for (int64_t k = threadIdx.x; k < CELL_WORDS * P.m; k += SB_T) s_cell[k] = src[k];
+            for (int64_t k = threadIdx.x; k < CELL_WORDS * P.m; k += SB_T)
+                s_cell[(k % CELL_WORDS) * LCELLS + k / CELL_WORDS] = src[k];
             __syncthreads();
         }
         if (staged) {
             // cells from LDS: two samples per step, both uniforms loaded
             // together (the second index clamped: no branch)
-            const Cell *sc = reinterpret_cast<const Cell *>(s_cell);
             for (int64_t sa = s0 + threadIdx.x; sa < e; sa += 2 * SB_T) {
                 const int64_t sb = sa + SB_T;
                 const uint64_t ua = __builtin_nontemporal_load(u + sa);
                 const uint64_t ub = __builtin_nontemporal_load(u + (sb < e ? sb : sa));
-                Cell ca = load_cell(sc, cell_in(P, ua));
-                Cell cb = load_cell(sc, cell_in(P, ub));
+                Cell ca = lds_cell(s_cell, (uint32_t)cell_in(P, ua));
+                Cell cb = lds_cell(s_cell, (uint32_t)cell_in(P, ub));
                 pin_cell(ca);
                 pin_cell(cb);
                 const Hit ha = resolve(nodes, wide, ca, P, ua, n_total);
@@ -461,48 +606,35 @@ __global__ __launch_bounds__(SB_T) __attribute__((amdgpu_waves_per_eu(8))) void 
     const bool staged = !mzero && M.m <= LCELLS;
     if (staged) {
         const uint4 *src = reinterpret_cast<const uint4 *>(cells + M.co);
-        for (int64_t k = threadIdx.x; k < CELL_WORDS * M.m; k += SB_T) s_cell[k] = src[k];
+        for (int64_t k = threadIdx.x; k < CELL_WORDS * M.m; k += SB_T)
+            s_cell[(k % CELL_WORDS) * LCELLS + k / CELL_WORDS] = src[k];
         __syncthreads();
     }
-    auto pair = [&](int64_t s, const u64x2 uu, const Cell &cr) {
-        i32x2 out = {-1, -1};
-        f64x2 pos = {__builtin_nan(""), __builtin_nan("")};
-        Hit hr;
-        hr.i = -1;
-        if (!mzero) hr = resolve(nodes, wide, cr, M, uu.x, n_total);
-        const int64_t r = hr.i - M.eo;
+    for (int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; s < S; s += T) {
+        const u64x2 uu = __builtin_nontemporal_load(up + s);
+        Cell cr = staged ? lds_cell(s_cell, (uint32_t)cell_in(M, uu.x))
+                         : load_cell(cells, mzero ? 0 : cell_index(M, uu.x));
+        pin_cell(cr);
+        const Hit hr = resolve(nodes, wide, cr, M, uu.x, n_total);
         // the marginal must have one weight per row distribution 1..D-1
-        if (hr.i >= 0 && 1 + r < D) {
-            out.x = (int32_t)r;
-            if (WANT_X) pos.x = position(M, hr, uu.x);
-            const Dist R = dists[1 + r];
-            Hit hc;
-            hc.i = -1;
-            if (!(R.flags & DIST_ZERO)) hc = descend(nodes, wide, cells, R, uu.y, n_total);
-            if (hc.i >= 0) {
-                out.y = (int32_t)(hc.i - R.eo);
-                if (WANT_X) pos.y = position(R, hc, uu.y);
-            }
+        const int32_t r = hr.i - (int32_t)M.eo;
+        const bool row = !mzero && hr.i >= 0 && 1 + r < D;
+        const Dist R = dists[row ? 1 + r : 0];
+        i32x2 out = {row ? r : -1, -1};
+        f64x2 pos = {__builtin_nan(""), __builtin_nan("")};
+        Cell cc = load_cell(cells, cell_index(R, uu.y));
+        if (WANT_X) {
+            const double y = position(M, hr, uu.x);
+            pos.x = row ? y : pos.x;
+        }
+        pin_cell(cc);
+        const Hit hc = resolve(nodes, wide, cc, R, uu.y, n_total);
+        if (row && hc.i >= 0 && !(R.flags & DIST_ZERO)) {
+            out.y = hc.i - (int32_t)R.eo;
+            if (WANT_X) pos.y = position(R, hc, uu.y);
         }
         __builtin_nontemporal_store(out, rcp + s);
         if (WANT_X) __builtin_nontemporal_store(pos, xyp + s);
-    };
-    const int64_t s_first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (staged) {
-        const Cell *sc = reinterpret_cast<const Cell *>(s_cell);
-        for (int64_t s = s_first; s < S; s += T) {
-            const u64x2 uu = __builtin_nontemporal_load(up + s);
-            Cell cr = load_cell(sc, cell_in(M, uu.x));
-            pin_cell(cr);
-            pair(s, uu, cr);
-        }
-    } else {
-        for (int64_t s = s_first; s < S; s += T) {
-            const u64x2 uu = __builtin_nontemporal_load(up + s);
-            Cell cr = load_cell(cells, mzero ? 0 : cell_index(M, uu.x));
-            pin_cell(cr);
-            pair(s, uu, cr);
-        }
     }
 }
 
@@ -588,18 +720,19 @@ hipError_t launch_sample(const Node *nodes, const Wide *wide, const Cell *cells,
         return hipGetLastError();
     }
     const dim3 g(batched ? grid_for((S + SCHUNK / 256 - 1) / (SCHUNK / 256)) : grid_for(S)), b(256);
-    if (batched && x)
-        hipLaunchKernelGGL((k_sample<true, true>), g, b, 0, st, nodes, wide, cells, dists, sample_off,
-                           D, n_total, u, S, idx, x);
-    else if (batched)
-        hipLaunchKernelGGL((k_sample<true, false>), g, b, 0, st, nodes, wide, cells, dists,
-                           sample_off, D, n_total, u, S, idx, x);
-    else if (x)
-        hipLaunchKernelGGL((k_sample<false, true>), g, b, 0, st, nodes, wide, cells, dists,
-                           sample_off, D, n_total, u, S, idx, x);
-    else
-        hipLaunchKernelGGL((k_sample<false, false>), g, b, 0, st, nodes, wide, cells, dists,
-                           sample_off, D, n_total, u, S, idx, x);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, g, b, 0, st, nodes, wide, cells, dists, sample_off, D, n_total, u, S, idx, x);
+    };
+    if (batched) {
+        if (x) go(k_sample<true, true, false>);
+        else go(k_sample<true, false, false>);
+    } else if (m_total * (int64_t)sizeof(Cell) <= QUAD_TABLE) {
+        if (x) go(k_sample<false, true, true>);
+        else go(k_sample<false, false, true>);
+    } else {
+        if (x) go(k_sample<false, true, false>);
+        else go(k_sample<false, false, false>);
+    }
     return hipGetLastError();
 }
 

@@ -1,0 +1,40 @@
+"""The sampling kernels at the edges between them: records fetched by quads of
+lanes or by single lanes (by the guide table's size), and waves that are not full."""
+import numpy as np
+import pytest
+
+from gpu_util import assert_samples, critical_u, note, random_weights, to_dev
+
+pytestmark = pytest.mark.gpu
+
+QUAD_CELLS = (12 << 20) // 64  # cells of the largest table fetched by quads
+
+
+@pytest.fixture(scope="module")
+def rtf():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_1901_05423_amd as rtf
+    rtf.lib()
+    return rtf
+
+
+@pytest.mark.parametrize("m", [1, 64, QUAD_CELLS - 1, QUAD_CELLS, QUAD_CELLS + 1])
+@pytest.mark.parametrize("count", [1, 3, 63, 64, 65, 257, 0])
+def test_record_fetch(rtf, orc, m, count):
+    note(f"record fetch m={m} count={count}")
+    rng = np.random.default_rng(m * 1000 + count)
+    w = random_weights(rng, 3000, zero_frac=0.2, skew=True)
+    w[:3] = 0  # several lower bounds of 0
+    f = rtf.build(to_dev(w), m)
+    f.check()
+    key = f.node_view().cpu().numpy()[:, 0].view(np.uint64)
+    u = critical_u(key, int(w.sum(dtype=np.uint64)), min(m, 2000))
+    if count:
+        u = rng.permutation(u)[:count]
+        u[-1] = 2 ** 64 - 1
+    idx, x = rtf.sample(f, to_dev(u))
+    only, _ = rtf.sample(f, to_dev(u), want_x=False)
+    i_ref, x_ref = orc.search(w, u)
+    assert_samples(idx.cpu().numpy(), x.cpu().numpy(), i_ref, x_ref)
+    assert np.array_equal(only.cpu().numpy(), i_ref)
