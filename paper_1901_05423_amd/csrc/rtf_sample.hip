@@ -29,6 +29,14 @@ constexpr int SB_T = 1024;      // threads of the kernels that stage records
 constexpr int LCELLS = 1024;    // staged records, 64 KB: two blocks per CU
 constexpr int STAGE_MIN = 2;    // samples per cell that make staging pay
 
+// A staged segment's average length from which staging pays.  Measured over
+// 1 to 4096 distributions of 64 to 1024 cells: at 4096 samples a distribution
+// the staged kernel takes 0.6 to 1.05 times the chunk kernel's time, at 2048
+// 0.8 to 1.4, at 512 2.4 to 2.7 (333 uneven tables of 16 to 2048 weights, 186K
+// samples: 85 us staged, 11 us in chunks), since a block then spends its time
+// finding and staging one short segment after another.
+constexpr int64_t STAGE_SEGMENT = 4096;
+
 // Bytes of guide table up to which single-distribution sampling fetches the
 // records by whole quads of lanes.  While the table fits the L2s the texture
 // path's 64 lines per wave load bound the kernel (2^26 samples with x from a
@@ -706,9 +714,10 @@ hipError_t launch_sample(const Node *nodes, const Wide *wide, const Cell *cells,
                          const uint64_t *u, int64_t S, int32_t *idx, double *x,
                          hipStream_t st) {
     const bool batched = sample_off != nullptr;
-    // many samples per cell and small distributions: stage the cells in LDS
-    // (two blocks of SB_T threads per CU)
-    if (batched && S >= (int64_t)STAGE_MIN * m_total && m_total <= (int64_t)LCELLS * D) {
+    // many samples per cell and per distribution, and small distributions:
+    // stage the cells in LDS (two blocks of SB_T threads per CU)
+    if (batched && S >= (int64_t)STAGE_MIN * m_total && S >= STAGE_SEGMENT * D &&
+        m_total <= (int64_t)LCELLS * D) {
         int64_t nb = (S + 4 * SB_T - 1) / (4 * SB_T);
         nb = nb < 512 ? nb : 512;
         if (x)

@@ -1,5 +1,6 @@
 """The sampling kernels at the edges between them: records fetched by quads of
-lanes or by single lanes (by the guide table's size), and waves that are not full."""
+lanes or by single lanes (by the guide table's size), waves that are not full,
+and batches on either side of the staging rule."""
 import numpy as np
 import pytest
 
@@ -38,3 +39,26 @@ def test_record_fetch(rtf, orc, m, count):
     i_ref, x_ref = orc.search(w, u)
     assert_samples(idx.cpu().numpy(), x.cpu().numpy(), i_ref, x_ref)
     assert np.array_equal(only.cpu().numpy(), i_ref)
+
+
+@pytest.mark.parametrize("collapsed", [False, True])
+@pytest.mark.parametrize("counts", [(4096, 4096, 4095), (4096, 4096, 4096), (0, 1, 12287), (8191, 0, 4097)])
+def test_staging_rule(rtf, orc, counts, collapsed):
+    note(f"staging rule counts={counts} collapsed={collapsed}")
+    rng = np.random.default_rng(sum(counts) + collapsed)
+    sizes, cells = [700, 4096, 31], [700, 1024, 31]
+    ws = [random_weights(rng, n, zero_frac=0.1, skew=True) for n in sizes]
+    off = lambda c: np.concatenate([[0], np.cumsum(c)]).astype(np.int64)  # noqa: E731
+    f = rtf.build_batched(to_dev(np.concatenate(ws)), to_dev(off(sizes)), to_dev(off(cells)))
+    if collapsed:
+        f.widen()
+    so = off(counts)
+    u = rng.integers(0, 2 ** 64, int(so[-1]), dtype=np.uint64)
+    u[-1] = 2 ** 64 - 1
+    idx, x = rtf.sample_batched(f, to_dev(so), to_dev(u))
+    idx, x = idx.cpu().numpy(), x.cpu().numpy()
+    for d, w in enumerate(ws):
+        a, b = so[d], so[d + 1]
+        if a < b:
+            i_ref, x_ref = orc.search(w, u[a:b])
+            assert_samples(idx[a:b], x[a:b], i_ref, x_ref)
