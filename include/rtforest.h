@@ -356,8 +356,8 @@ rtf_status rtf_backward_static(const rtf_forest *f, const int64_t *sample_off,
  * of cell j, alias_j the rest.  Built by Vose's two-worklist method in a
  * fixed order (small items, of mass below W, and large ones on two stacks in
  * increasing index order; each step pairs the top of both and pushes the
- * large item back by its remaining mass), serial per distribution as the
- * paper notes known setups are.
+ * large item back by its remaining mass); the pairing this gives is computed
+ * from prefix sums of the deficits and excesses.
  */
 typedef struct rtf_alias_table {
     int32_t D;
@@ -377,9 +377,9 @@ size_t rtf_alias_workspace_bytes(int32_t D, int64_t n_total);
  *             in rtf_build_batched (NULL with D == 1)
  *   ws        rtf_alias_workspace_bytes(D, n_total) bytes, 256-byte aligned;
  *             it holds the tables afterwards
- * One thread per distribution runs the serial setup, so a distribution of n
- * items costs n dependent steps on one thread: the call suits many small or
- * medium tables (the rows of a 2D map), not one table of millions of items.
+ * One block (for batches of tiny tables, one thread) sets up a distribution:
+ * the call suits many small or medium tables (the rows of a 2D map), not one
+ * table of millions of items.
  * A distribution with W = 0 is reported by rtf_alias_export as
  * RTF_ERR_ZERO_TOTAL and samples to -1.
  */
