@@ -9,9 +9,13 @@
 //   dL/dv_k = A_d - sum_{j > k} B_j - D_k,
 //   A_d = sum_s a_s xi_s,  B_j = sum_{i_s = j} a_s,  D_j = sum_{i_s = j} a_s frac_s.
 // k_bscatter accumulates A, B, D; k_bhead, k_bcarry and k_bfinal do the
-// suffix sum of B segmented by distribution.  A block whose samples all belong to one distribution
-// of at most LBINS elements sums B and D in LDS first and adds each bin to
+// suffix sum of B segmented by distribution.  A block whose samples' distributions
+// hold at most LBINS elements sums B and D in LDS first and adds each bin to
 // global memory once; otherwise every sample adds with FP64 global atomics.
+// Measured (whole pass, 2^24 samples of 4096 weights 132 -> 105 us; 2^20 of
+// 65536 weights 733 -> 72; 30 distributions of 20 weights, 3000 samples each,
+// 637 -> 26; 256 of 300 weights, 3000 each, 963 -> 33): the chunks, the pair
+// atomics and the bins of several distributions below.
 #include "rtf_internal.h"
 
 namespace rtf {
@@ -21,7 +25,6 @@ namespace {
 constexpr int CB = 1024;          // threads of the combining kernel (fewer chunk steps)
 constexpr int SB = 1024;          // threads of a scatter block
 constexpr int ILP = 2;            // samples a scatter thread loads at once
-constexpr int CHUNK = SB * 128;   // samples per scatter block
 constexpr int LBINS = 4096;       // bins a block can sum in LDS (2 x 32 KB)
 
 __device__ inline int32_t find_segment_in(const int64_t *off, int32_t lo, int32_t hi, int64_t i) {
@@ -33,13 +36,35 @@ __device__ inline int32_t find_segment_in(const int64_t *off, int32_t lo, int32_
     return lo;
 }
 
-__global__ void k_bzero(double *B, double *Dv, int64_t n, double *A, int32_t D) {
+__global__ void k_bzero(double2 *BD, int64_t n, double *A, int32_t D) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        B[i] = 0.0;
-        Dv[i] = 0.0;
+        BD[i] = make_double2(0.0, 0.0);
         if (i < D) A[i] = 0.0;
     }
+}
+
+// Adds (a, d) to BD[i] for every lane with i >= 0.  The L2s take FP64 atomics
+// at about 22 G requests a second whatever the array's size, so a sample's two
+// sums lie side by side and neighbouring lanes add them in one request: first
+// both lanes of a pair for the even lane's sample, then for the odd one's.
+// (Whole pairs of lanes must call it together.)  One distribution of 2^22
+// weights, 2^24 samples, the whole pass: 1509 us with an atomic each, 837 so.
+__device__ inline double from_pair(double x) {
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)b, 0xb1, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(b >> 32), 0xb1, 0xf, 0xf, true);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+__device__ inline void add_pairs(double2 *BD, int32_t i, double a, double d) {
+    const bool odd = threadIdx.x & 1;
+    const int32_t pi = __builtin_amdgcn_mov_dpp(i, 0xb1, 0xf, 0xf, true);
+    const double pa = from_pair(a), pd = from_pair(d);
+    double *base = reinterpret_cast<double *>(BD) + odd;
+    const int32_t i0 = odd ? pi : i, i1 = odd ? i : pi;
+    const double v0 = odd ? pd : a, v1 = odd ? d : pa;
+    if (i0 >= 0) unsafeAtomicAdd(base + 2 * (int64_t)i0, v0);
+    if (i1 >= 0) unsafeAtomicAdd(base + 2 * (int64_t)i1, v1);
 }
 
 template <int NT>
@@ -60,23 +85,32 @@ __device__ inline double block_sum(double x, double *s_red) {
 // apart: all their stream loads are issued, then all their key loads, before
 // any arithmetic, since the kernel is bound by the latency of these two
 // dependent rounds (64 KB of LDS bins leave room for two blocks per CU).
-// UNI: the block's samples all belong to distribution d0, whose parameters
-// then stay in scalar registers.  acc accumulates a xi for distribution acc_d
-// and is flushed to A when the distribution changes.
-template <bool UNI>
+// ONE: the block's samples all belong to distribution d0, whose parameters
+// then stay in scalar registers, and acc sums a xi.  MANY: they belong to
+// several, found by a search per sample; a xi goes to the LDS bins s_a, one
+// per distribution from d0 on (na of them; past those, or with na = 0, to A
+// itself), since thousands of threads adding to a few words of A would
+// serialise.  MANY_LDS: as MANY, and the elements of those distributions,
+// e0 .. e0 + n_el - 1, fit the LDS bins: B and D are summed there, and the
+// partial sums are staged as in scatter_local.
+enum ScatterMode { ONE, MANY, MANY_LDS };
+template <ScatterMode MODE>
 __device__ inline void scatter_samples(const Node *__restrict__ nodes, const Dist *__restrict__ dists,
                                        const int64_t *__restrict__ soff, const uint64_t *__restrict__ u,
                                        const int32_t *__restrict__ idx, const double *__restrict__ gx,
                                        const double *__restrict__ scale, int64_t c0, int64_t c1,
-                                       int32_t d0, int32_t d_last, double *B, double *Dv, double *A,
-                                       double &acc, int32_t &acc_d) {
+                                       int32_t d0, int32_t d_last, double2 *BD, double *A, double &acc,
+                                       double *s_a, int32_t na, double *s_b, double *s_d, const uint32_t *s_clo,
+                                       int64_t e0) {
+    constexpr bool UNI = MODE == ONE;
     int32_t d = d0;  // distribution of the thread's latest sample
     int64_t dend = UNI ? c1 : soff[d + 1];
     // the parameters are copied into registers: read through a reference they
     // would be fetched again after every atomic, one round trip each
     const Dist P0 = dists[d0];
     const double sc0 = scale[d0];
-    for (int64_t s0 = c0 + threadIdx.x; s0 < c1; s0 += (int64_t)ILP * SB) {
+    for (int64_t sb = c0; sb < c1; sb += (int64_t)ILP * SB) {  // the whole block steps together
+        const int64_t s0 = sb + threadIdx.x;
         int32_t li[ILP], dq[ILP];
         uint64_t us[ILP];
         double g[ILP];
@@ -112,13 +146,14 @@ __device__ inline void scatter_samples(const Node *__restrict__ nodes, const Dis
         for (int q = 0; q < ILP; ++q) {
             const Dist &P = Pq[q];
             const bool valid = li[q] >= 0 && li[q] < P.n && !(P.flags & DIST_ZERO);
+            if (!valid) li[q] = -1;
+            if (MODE == MANY_LDS) continue;
             const int64_t lc = valid ? li[q] : 0;
             const bool last = lc + 1 >= P.n;
             const int64_t i = P.eo + lc;
             k0[q] = nodes[i].key;
             const uint64_t kn = nodes[last ? i : i + 1].key;
             k1[q] = last ? ~0ull : kn;
-            if (!valid) li[q] = -1;
         }
         // the arithmetic runs for every sample (a skipped one yields values
         // that are discarded), which keeps the compiler from sinking the
@@ -127,26 +162,34 @@ __device__ inline void scatter_samples(const Node *__restrict__ nodes, const Dis
         for (int q = 0; q < ILP; ++q) {
             const Dist &P = Pq[q];
             const uint64_t W = P.W;
-            const uint64_t Ci = mulhi64(k0[q], W);
-            const uint64_t Cn = k1[q] != ~0ull ? mulhi64(k1[q], W) : W;
+            const bool ok = li[q] >= 0;
+            const int64_t i = P.eo + (ok ? li[q] : 0);
+            uint32_t ci, cn;
+            if (MODE == MANY_LDS) {
+                ci = s_clo[i - e0];
+                cn = li[q] + 1 < P.n ? s_clo[i - e0 + (ok ? 1 : 0)] : (uint32_t)W;
+            } else {
+                ci = (uint32_t)mulhi64(k0[q], W);
+                cn = (uint32_t)(k1[q] != ~0ull ? mulhi64(k1[q], W) : W);
+            }
             const uint64_t t = mulhi64(us[q], W), lo = us[q] * W;
             // w_i < 2^32 for a sampled i (a skipped sample's values are dropped)
-            const double wi = (double)(uint32_t)(Cn - Ci);
+            const double wi = (double)(cn - ci);
             const double rw = recip_small(__builtin_fmax(wi, 1.0));
-            const double frac = ((double)(uint32_t)(t - Ci) + ldexp((double)lo, -64)) * rw;
+            const double frac = ((double)((uint32_t)t - ci) + ldexp((double)lo, -64)) * rw;
             const double xi = ldexp((double)us[q], -64);
             const double a = g[q] * (sq[q] / (double)P.n) * rw;
-            const bool ok = li[q] >= 0;
-            if (!UNI && ok && dq[q] != acc_d) {
-                if (acc != 0.0) unsafeAtomicAdd(A + acc_d, acc);
-                acc = 0.0;
-                acc_d = dq[q];
+            if (UNI) acc += ok ? a * xi : 0.0;
+            if (!UNI && ok) {
+                if (dq[q] - d0 < na) atomicAdd(s_a + (dq[q] - d0), a * xi);
+                else unsafeAtomicAdd(A + dq[q], a * xi);
             }
-            acc += ok ? a * xi : 0.0;
-            if (!ok) continue;
-            const int64_t i = P.eo + li[q];
-            unsafeAtomicAdd(B + i, a);
-            unsafeAtomicAdd(Dv + i, a * frac);
+            if (MODE != MANY_LDS) {
+                add_pairs(BD, ok ? (int32_t)i : -1, a, a * frac);
+            } else if (ok) {
+                atomicAdd(s_b + (i - e0), a);
+                atomicAdd(s_d + (i - e0), a * frac);
+            }
         }
     }
 }
@@ -205,12 +248,21 @@ __device__ inline void scatter_local(const Node *__restrict__ nodes, const Dist 
     }
 }
 
+// the LDS bins of n elements into global memory, a pair of lanes per element
+__device__ inline void flush_bins(const double *s_b, const double *s_d, int64_t n, double2 *BD) {
+    double *out = reinterpret_cast<double *>(BD);
+    for (int64_t k = threadIdx.x; k < 2 * n; k += SB) {
+        const double v = (k & 1) ? s_d[k >> 1] : s_b[k >> 1];
+        if (v != 0.0) unsafeAtomicAdd(out + k, v);
+    }
+}
+
 template <bool BATCHED>
 __global__ __launch_bounds__(SB) __attribute__((amdgpu_waves_per_eu(8))) void k_bscatter(
     const Node *__restrict__ nodes, const Dist *__restrict__ dists, int32_t D,
     const int64_t *__restrict__ soff, const uint64_t *__restrict__ u, const int32_t *__restrict__ idx,
-    const double *__restrict__ gx, int64_t S, const double *__restrict__ scale, double *B, double *Dv,
-    double *A) {
+    const double *__restrict__ gx, int64_t S, const double *__restrict__ scale, double2 *BD, double *A,
+    int64_t chunk) {
     // 80 KB, so that two blocks fit in a CU's 160 KB; the block sum reuses
     // the staged partial sums' space
     __shared__ double s_b[LBINS], s_d[LBINS];
@@ -218,36 +270,59 @@ __global__ __launch_bounds__(SB) __attribute__((amdgpu_waves_per_eu(8))) void k_
     double *s_red = reinterpret_cast<double *>(s_clo);
     // chunks numbered per XCD: the 8 or so blocks of one distribution share
     // one L2
-    const int64_t c0 = xcd_block() * CHUNK;
-    const int64_t c1 = c0 + CHUNK < S ? c0 + CHUNK : S;
+    const int64_t c0 = xcd_block() * chunk;
+    const int64_t c1 = c0 + chunk < S ? c0 + chunk : S;
     const int32_t d_first = BATCHED ? find_segment_in(soff, 0, D, c0) : 0;
     const int32_t d_last = BATCHED ? find_segment_in(soff, d_first, D, c1 - 1) : 0;
-    const bool uniform = d_first == d_last;
     const Dist P0 = dists[d_first];
-    const bool local = uniform && P0.n <= LBINS;  // uniform across the block
-    int32_t acc_d = d_first;
     double acc = 0.0;
-    if (local)
-        scatter_local(nodes, P0, scale[d_first], u, idx, gx, c0, c1, s_b, s_d, s_clo, acc);
-    else if (uniform)
-        scatter_samples<true>(nodes, dists, soff, u, idx, gx, scale, c0, c1, d_first, d_last, B, Dv, A, acc,
-                              acc_d);
-    else
-        scatter_samples<false>(nodes, dists, soff, u, idx, gx, scale, c0, c1, d_first, d_last, B, Dv, A, acc,
-                               acc_d);
-    __syncthreads();
-    if (local) {
-        for (int64_t k = threadIdx.x; k < P0.n; k += SB) {
-            if (s_b[k] != 0.0) unsafeAtomicAdd(B + P0.eo + k, s_b[k]);
-            if (s_d[k] != 0.0) unsafeAtomicAdd(Dv + P0.eo + k, s_d[k]);
-        }
-    }
-    if (uniform) {
+    if (!BATCHED || d_first == d_last) {
+        const bool local = P0.n <= LBINS;  // uniform across the block
+        if (local)
+            scatter_local(nodes, P0, scale[d_first], u, idx, gx, c0, c1, s_b, s_d, s_clo, acc);
+        else
+            scatter_samples<ONE>(nodes, dists, soff, u, idx, gx, scale, c0, c1, d_first, d_last, BD, A, acc,
+                                 nullptr, 0, nullptr, nullptr, nullptr, 0);
+        __syncthreads();
+        if (local) flush_bins(s_b, s_d, P0.n, BD + P0.eo);
         const double t = block_sum<SB>(acc, s_red);
         if (threadIdx.x == 0 && t != 0.0) unsafeAtomicAdd(A + d_first, t);
-    } else if (acc != 0.0) {
-        unsafeAtomicAdd(A + acc_d, acc);
+        return;
     }
+    if (!BATCHED) return;
+    const int64_t nd = d_last - d_first + 1, e0 = P0.eo;
+    const int64_t n_el = dists[d_last].eo + dists[d_last].n - e0;
+    if (n_el + nd <= LBINS) {
+        // the elements' bins, then the distributions' in s_b
+        double *s_a = s_b + n_el;
+        for (int64_t k = threadIdx.x; k < n_el + nd; k += SB) s_b[k] = s_d[k] = 0.0;
+        for (int64_t k = threadIdx.x; k < n_el; k += SB) {
+            int32_t lo = d_first, hi = d_last + 1;  // the element's distribution
+            while (hi - lo > 1) {
+                const int32_t mid = (lo + hi) >> 1;
+                if (dists[mid].eo <= e0 + k) lo = mid;
+                else hi = mid;
+            }
+            const uint64_t key = nodes[e0 + k].key, W = dists[lo].W;
+            s_clo[k] = (uint32_t)(key == ~0ull ? W : mulhi64(key, W));
+        }
+        __syncthreads();
+        scatter_samples<MANY_LDS>(nodes, dists, soff, u, idx, gx, scale, c0, c1, d_first, d_last, BD, A, acc, s_a,
+                                  (int32_t)nd, s_b, s_d, s_clo, e0);
+        __syncthreads();
+        flush_bins(s_b, s_d, n_el, BD + e0);
+        for (int64_t k = threadIdx.x; k < nd; k += SB)
+            if (s_a[k] != 0.0) unsafeAtomicAdd(A + d_first + k, s_a[k]);
+        return;
+    }
+    const int32_t na = (int32_t)(nd < LBINS ? nd : LBINS);
+    for (int32_t k = threadIdx.x; k < na; k += SB) s_b[k] = 0.0;
+    __syncthreads();
+    scatter_samples<MANY>(nodes, dists, soff, u, idx, gx, scale, c0, c1, d_first, d_last, BD, A, acc, s_b, na,
+                          nullptr, nullptr, nullptr, 0);
+    __syncthreads();
+    for (int32_t k = threadIdx.x; k < na; k += SB)
+        if (s_b[k] != 0.0) unsafeAtomicAdd(A + d_first + k, s_b[k]);
 }
 
 // ---------------------------------------------------------------------------
@@ -338,7 +413,7 @@ __device__ inline void chunk_dists(const int64_t *eoff, int32_t D, int64_t c0, i
 // element; link[c]: bit 0 the chunk lies inside that distribution, bit 1 the
 // distribution of its last element continues into the next chunk.
 __global__ __launch_bounds__(CB) void k_bhead(const int64_t *__restrict__ eoff, int32_t D,
-                                              int64_t n, const double *__restrict__ B,
+                                              int64_t n, const double2 *__restrict__ BD,
                                               double *__restrict__ head, int32_t *__restrict__ link) {
     __shared__ int32_t s_d[2];
     __shared__ double s_red[CB / 64];
@@ -349,7 +424,7 @@ __global__ __launch_bounds__(CB) void k_bhead(const int64_t *__restrict__ eoff, 
     const int64_t e_first = eoff[dfirst + 1], e_last = eoff[dlast + 1];
     const int64_t hend = e_first < c1 ? e_first : c1;
     double x = 0.0;
-    for (int64_t k = c0 + threadIdx.x; k < hend; k += CB) x += B[k];
+    for (int64_t k = c0 + threadIdx.x; k < hend; k += CB) x += BD[k].x;
     const double t = block_sum<CB>(x, s_red);
     if (threadIdx.x == 0) {
         head[c] = t;
@@ -398,8 +473,7 @@ __global__ __launch_bounds__(CB) void k_bcarry(const double *__restrict__ head,
 // c1 - 1 - (CE T + e), e = 0 .. CE-1 (scan order is descending k); a term
 // starts a segment at the last element of its distribution.
 __global__ __launch_bounds__(CB) void k_bfinal(const int64_t *__restrict__ eoff, int32_t D,
-                                               int64_t n, const double *__restrict__ B,
-                                               const double *__restrict__ Dv,
+                                               int64_t n, const double2 *__restrict__ BD,
                                                const double *__restrict__ A,
                                                const double *__restrict__ carry,
                                                double *__restrict__ grad) {
@@ -418,7 +492,7 @@ __global__ __launch_bounds__(CB) void k_bfinal(const int64_t *__restrict__ eoff,
     const double cin = carry[c];
     int64_t kk[CE];
     int32_t dq[CE];
-    double b[CE];
+    double2 b[CE];
     SegSum term[CE], agg{0.0, 0};
     // distribution of the thread's first (highest) element, then downwards
     const int64_t ktop = c1 - 1 - (int64_t)CE * threadIdx.x;
@@ -436,8 +510,8 @@ __global__ __launch_bounds__(CB) void k_bfinal(const int64_t *__restrict__ eoff,
         const bool ok = k >= c0;
         while (ok && q > 0 && s_off[q - 1] > k) --q;
         dq[e] = q;
-        b[e] = ok ? B[k] : 0.0;
-        term[e] = SegSum{b[e], ok && s_off[q] == k + 1 ? 1 : 0};
+        b[e] = ok ? BD[k] : make_double2(0.0, 0.0);
+        term[e] = SegSum{b[e].x, ok && s_off[q] == k + 1 ? 1 : 0};
         agg = seg_join(agg, term[e]);
     }
     SegSum total;
@@ -448,9 +522,23 @@ __global__ __launch_bounds__(CB) void k_bfinal(const int64_t *__restrict__ eoff,
         const int64_t k = kk[e];
         if (k < c0) continue;
         const int32_t d = dfirst + dq[e];
-        const double right = run.v - b[e] + (d == dlast ? cin : 0.0);
-        grad[k] = A[d] - right - Dv[k];
+        const double right = run.v - b[e].x + (d == dlast ? cin : 0.0);
+        grad[k] = A[d] - right - b[e].y;
     }
+}
+
+// Samples per scatter block.  Two blocks per CU hide the loads' latency, so a
+// small S is cut into 512 (2^16 samples on one block: 338 us, now 31; 2^20 on
+// eight: 660 and 114), down to one step of a block; a chunk that is
+// summed in LDS bins also has to be worth the bins' flush, two atomics per
+// element (4096 weights, 2^20 samples: 34 us in chunks of 8192, 55 in chunks
+// of 2048), unless that would span several distributions.
+int64_t scatter_chunk(int64_t n_total, int32_t D, int64_t S) {
+    const int64_t step = (int64_t)ILP * SB, avg = n_total / D;
+    int64_t c = (S / 512 + SB - 1) / SB * SB;
+    const int64_t low = avg <= LBINS && S >= 8 * avg * D && 2 * avg > step ? 2 * avg : step;
+    c = c < low ? low : c;
+    return c < 128 * SB ? c : 128 * SB;
 }
 
 }  // namespace
@@ -462,23 +550,23 @@ hipError_t launch_backward(const Node *nodes, const Dist *dists, const int64_t *
                            hipStream_t st) {
     int64_t zb = (n_total + 255) / 256;
     if (zb > 4096) zb = 4096;
-    hipLaunchKernelGGL(k_bzero, dim3((unsigned)zb), dim3(256), 0, st, w.B, w.Dv, n_total, w.A,
-                       D);
+    hipLaunchKernelGGL(k_bzero, dim3((unsigned)zb), dim3(256), 0, st, w.BD, n_total, w.A, D);
     if (S > 0) {
-        const int64_t nb = (S + CHUNK - 1) / CHUNK;
+        const int64_t chunk = scatter_chunk(n_total, D, S);
+        const int64_t nb = (S + chunk - 1) / chunk;
         if (sample_off)
             hipLaunchKernelGGL(k_bscatter<true>, dim3((unsigned)nb), dim3(SB), 0, st, nodes, dists,
-                               D, sample_off, u, idx, gx, S, scale, w.B, w.Dv, w.A);
+                               D, sample_off, u, idx, gx, S, scale, w.BD, w.A, chunk);
         else
             hipLaunchKernelGGL(k_bscatter<false>, dim3((unsigned)nb), dim3(SB), 0, st, nodes, dists,
-                               D, sample_off, u, idx, gx, S, scale, w.B, w.Dv, w.A);
+                               D, sample_off, u, idx, gx, S, scale, w.BD, w.A, chunk);
     }
     const int64_t nch = backward_chunks(n_total);
-    hipLaunchKernelGGL(k_bhead, dim3((unsigned)nch), dim3(CB), 0, st, elem_off, D, n_total, w.B,
+    hipLaunchKernelGGL(k_bhead, dim3((unsigned)nch), dim3(CB), 0, st, elem_off, D, n_total, w.BD,
                        w.head, w.link);
     hipLaunchKernelGGL(k_bcarry, dim3(1), dim3(CB), 0, st, w.head, w.link, nch, w.carry);
-    hipLaunchKernelGGL(k_bfinal, dim3((unsigned)nch), dim3(CB), 0, st, elem_off, D, n_total, w.B,
-                       w.Dv, w.A, w.carry, grad_w);
+    hipLaunchKernelGGL(k_bfinal, dim3((unsigned)nch), dim3(CB), 0, st, elem_off, D, n_total, w.BD,
+                       w.A, w.carry, grad_w);
     return hipGetLastError();
 }
 
