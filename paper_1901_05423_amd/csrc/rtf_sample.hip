@@ -40,8 +40,8 @@ constexpr int64_t STAGE_SEGMENT = 4096;
 // Bytes of guide table up to which single-distribution sampling fetches the
 // records by whole quads of lanes.  While the table fits the L2s the texture
 // path's 64 lines per wave load bound the kernel (2^26 samples with x from a
-// 1 MiB table: 798 us with a record per lane, 694 by quads; index only 658 and
-// 529); from about 16 MiB the lines from the fabric do, and the quads'
+// 1 MiB table: 795 us with a record per lane, 679 by quads; index only 659 and
+// 516); from about 16 MiB the lines from the fabric do, and the quads'
 // transposition only costs (256 MiB table: 1430 us a record per lane, 1440 by
 // quads; index only 1339 and 1351).
 constexpr int64_t QUAD_TABLE = 12 << 20;
@@ -78,34 +78,47 @@ __device__ inline Node load_node(const Node *nodes, int64_t j) {
     return r;
 }
 
-__device__ inline Cell cell_of_words(const uint4 *v) {
-    Cell r;
-#pragma unroll
-    for (int w = 0; w < CELL_WORDS; ++w) {
-        r.k[2 * w] = ((uint64_t)v[w].y << 32) | v[w].x;
-        if (w + 1 < CELL_WORDS) r.k[2 * w + 1] = ((uint64_t)v[w].w << 32) | v[w].z;
-    }
-    r.ref = (int32_t)v[CELL_WORDS - 1].z;
-    r.aux = (int32_t)v[CELL_WORDS - 1].w;
-    return r;
-}
+// A record as it was loaded, its 16-byte words in flight until cell_of().
+typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+struct Words {
+    u64x2 v[CELL_WORDS];
+};
 
-__device__ inline Cell load_cell(const Cell *cells, int64_t g) {
-    const uint4 *p = reinterpret_cast<const uint4 *>(cells + g);
-    uint4 v[CELL_WORDS];
+__device__ inline Words load_words(const Cell *cells, int64_t g) {
+    const u64x2 *p = reinterpret_cast<const u64x2 *>(cells + g);
+    Words r;
 #pragma unroll
-    for (int w = 0; w < CELL_WORDS; ++w) v[w] = p[w];  // all in flight together
-    return cell_of_words(v);
+    for (int w = 0; w < CELL_WORDS; ++w) r.v[w] = p[w];  // all in flight together
+    return r;
 }
 
 // Record c of a staged table: word w of every record lies in a plane of its
 // own, [CELL_WORDS][LCELLS], so that a wave's 16-byte reads of one word
 // spread over all banks (in record order they would fall on a quarter).
-__device__ inline Cell lds_cell(const uint4 *s_cell, uint32_t c) {
-    uint4 v[CELL_WORDS];
+__device__ inline Words lds_words(const u64x2 *s_cell, uint32_t c) {
+    Words r;
 #pragma unroll
-    for (int w = 0; w < CELL_WORDS; ++w) v[w] = s_cell[w * LCELLS + c];
-    return cell_of_words(v);
+    for (int w = 0; w < CELL_WORDS; ++w) r.v[w] = s_cell[w * LCELLS + c];
+    return r;
+}
+
+// The record, once its words have arrived.  Every word is marked as used here,
+// whole, so that its loads complete together (one wait) and are made once:
+// the compiler otherwise splits the record load along the branches that use
+// each word (up to three round trips to the same line, one after another) or
+// loads a half of a word a second time.
+__device__ inline Cell cell_of(Words &r) {
+#pragma unroll
+    for (int w = 0; w < CELL_WORDS; ++w) asm volatile("" : "+v"(r.v[w]));
+    Cell c;
+#pragma unroll
+    for (int w = 0; w < CELL_WORDS; ++w) {
+        c.k[2 * w] = r.v[w].x;
+        if (w + 1 < CELL_WORDS) c.k[2 * w + 1] = r.v[w].y;
+    }
+    c.ref = (int32_t)(uint32_t)r.v[CELL_WORDS - 1].y;
+    c.aux = (int32_t)(uint32_t)(r.v[CELL_WORDS - 1].y >> 32);
+    return c;
 }
 
 // One 4x4 transposition step inside every quad of lanes: out0 takes a from
@@ -127,15 +140,16 @@ __device__ inline void quad_swap4(uint4 &a, uint4 &b, bool odd) {
     quad_swap<CTRL>(a.w, b.w, odd);
 }
 
-// Every lane's 64-byte record base[g], fetched by whole quads of lanes: in
+// Every lane's record cells[g], fetched by whole quads of lanes: in
 // step q the four lanes of a quad load the four 16-byte words of lane q's
 // record, so that a wave instruction touches 16 lines instead of 64, and a
 // 4x4 transposition inside the quads hands every lane its own words.  All
 // lanes of a quad must call it together.
-__device__ inline void load_record_quad(const void *base, uint32_t g, uint4 *v) {
-    static_assert(CELL_WORDS == 4 && sizeof(Dist) == 64, "one word of a record per lane of a quad");
+__device__ inline Words load_words_quad(const Cell *cells, uint32_t g) {
+    static_assert(CELL_WORDS == 4, "one word of a record per lane of a quad");
+    uint4 v[CELL_WORDS];
     const uint32_t lane = threadIdx.x;
-    const char *p = reinterpret_cast<const char *>(base) + 16 * (lane & 3);
+    const char *p = reinterpret_cast<const char *>(cells) + 16 * (lane & 3);
     const uint32_t g0 = (uint32_t)__builtin_amdgcn_mov_dpp((int)g, 0x00, 0xf, 0xf, true);
     const uint32_t g1 = (uint32_t)__builtin_amdgcn_mov_dpp((int)g, 0x55, 0xf, 0xf, true);
     const uint32_t g2 = (uint32_t)__builtin_amdgcn_mov_dpp((int)g, 0xaa, 0xf, 0xf, true);
@@ -149,22 +163,23 @@ __device__ inline void load_record_quad(const void *base, uint32_t g, uint4 *v) 
     quad_swap4<0xb1>(v[2], v[3], o1);
     quad_swap4<0x4e>(v[0], v[2], o2);  // quad_perm 2 3 0 1
     quad_swap4<0x4e>(v[1], v[3], o2);
-}
-
-__device__ inline Cell load_cell_quad(const Cell *cells, uint32_t g) {
-    uint4 v[4];
-    load_record_quad(cells, g, v);
-    return cell_of_words(v);
-}
-
-// Marks every word of a record as used here, so that the record's loads,
-// issued before, complete together (one wait).  Without it, when x is not
-// wanted, the compiler splits the record load along the branches that use
-// each word: up to three round trips to the same line, one after another.
-__device__ inline void pin_cell(Cell &c) {
+    Words r;
 #pragma unroll
-    for (int t = 0; t < CELL_KEYS; ++t) asm volatile("" : "+v"(c.k[t]));
-    asm volatile("" : "+v"(c.ref), "+v"(c.aux));
+    for (int w = 0; w < CELL_WORDS; ++w) {
+        r.v[w].x = ((uint64_t)v[w].y << 32) | v[w].x;
+        r.v[w].y = ((uint64_t)v[w].w << 32) | v[w].z;
+    }
+    return r;
+}
+
+// Whether the wave's samples are (by its first and last lane) in order within
+// a few cells, as those of sorted or stratified uniforms are: their records
+// share lines as they are, and the quads' transposition would only cost (2^26
+// ordered indices from a 1 MiB table: 281 us by quads, 267 a record
+// per lane).
+__device__ inline bool narrow_wave(uint32_t g) {
+    const uint32_t a = __builtin_amdgcn_readlane(g, 0), b = __builtin_amdgcn_readlane(g, 63);
+    return b - a < 32u;
 }
 
 // A sampled leaf with the keys of its interval's two ends (KEY_END for the
@@ -342,9 +357,8 @@ __device__ inline Hit resolve(const Node *nodes, const Wide *wide, const Cell &c
 
 __device__ inline Hit descend(const Node *nodes, const Wide *wide, const Cell *cells, const Dist &P,
                               uint64_t u, int64_t n_total) {
-    Cell c = load_cell(cells, cell_index(P, u));
-    pin_cell(c);
-    return resolve(nodes, wide, c, P, u, n_total);
+    Words r = load_words(cells, cell_index(P, u));
+    return resolve(nodes, wide, cell_of(r), P, u, n_total);
 }
 
 // x = (i + ((t - C_i) + lo * 2^-64) / w_i) / n with t:lo = u * W, where
@@ -400,29 +414,46 @@ __global__ __launch_bounds__(256) void k_sample(const Node *__restrict__ nodes,
     if (!BATCHED) {
         const Dist P = dists[0];
         const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-        const bool zero = P.flags & DIST_ZERO;
+        auto sample = [&](uint64_t us) {
+            const int64_t g = cell_in(P, us);
+            Words r;
+            if (QUAD && !narrow_wave((uint32_t)g)) r = load_words_quad(cells, (uint32_t)g);
+            else r = load_words(cells, g);
+            return resolve(nodes, wide, cell_of(r), P, us, n_total);
+        };
+        auto put = [&](int64_t s, const Hit &h, uint64_t us) {
+            __builtin_nontemporal_store(h.i < 0 ? (int32_t)-1 : h.i - (int32_t)P.eo, idx + s);
+            if (WANT_X) {
+                const double px = position(P, h, us);
+                __builtin_nontemporal_store(h.i < 0 ? (double)__builtin_nan("") : px, x + s);
+            }
+        };
         int64_t s0 = (int64_t)blockIdx.x * blockDim.x;
-        if (s0 >= S) return;
-        auto at = [&](int64_t s) { return __builtin_nontemporal_load(u + (s < S ? s : S - 1)); };
-        uint64_t next = at(s0 + threadIdx.x);
-        for (; s0 < S; s0 += stride) {
+        if (P.flags & DIST_ZERO) {
+            Hit none;
+            none.i = -1;
+            none.lo = none.hi = 0;
+            for (int64_t s = s0 + threadIdx.x; s < S; s += stride) put(s, none, 0);
+            return;
+        }
+        // Whole steps of a block, the next step's uniform loaded a step ahead.
+        // Neither its address nor the stores depend on the lane's place, so
+        // that no wait for the uniform waits for the stores issued after it.
+        const int64_t whole = S - 255;
+        if (s0 < whole) {
+            uint64_t next = __builtin_nontemporal_load(u + s0 + threadIdx.x);
+            for (; s0 < whole; s0 += stride) {
+                const uint64_t us = next;
+                next = __builtin_nontemporal_load(u + (s0 + stride < whole ? s0 + stride : s0) + threadIdx.x);
+                const Hit h = sample(us);
+                put(s0 + threadIdx.x, h, us);
+            }
+        }
+        if (s0 < S) {  // the last, part of a step: lanes past the end repeat the last sample
             const int64_t s = s0 + threadIdx.x;
-            const uint64_t us = next;
-            next = at(s + stride);
-            Hit h;
-            h.i = -1;
-            if (!zero) {
-                Cell c = QUAD ? load_cell_quad(cells, (uint32_t)cell_in(P, us)) : load_cell(cells, cell_in(P, us));
-                pin_cell(c);
-                h = resolve(nodes, wide, c, P, us, n_total);
-            }
-            if (s < S) {
-                __builtin_nontemporal_store(h.i < 0 ? (int32_t)-1 : h.i - (int32_t)P.eo, idx + s);
-                if (WANT_X) {
-                    const double px = position(P, h, us);
-                    __builtin_nontemporal_store(h.i < 0 ? (double)__builtin_nan("") : px, x + s);
-                }
-            }
+            const uint64_t us = u[s < S ? s : S - 1];
+            const Hit h = sample(us);
+            if (s < S) put(s, h, us);
         }
         return;
     }
@@ -449,10 +480,9 @@ __global__ __launch_bounds__(256) void k_sample(const Node *__restrict__ nodes,
         const uint64_t ua = __builtin_nontemporal_load(u + sa);
         const uint64_t ub = __builtin_nontemporal_load(u + (has_b ? sb : sa));  // no branch
         const bool za = Pa.flags & DIST_ZERO, zb = Pb.flags & DIST_ZERO;
-        Cell ca = load_cell(cells, za ? 0 : cell_index(Pa, ua));
-        Cell cb = load_cell(cells, zb ? 0 : cell_index(Pb, ub));
-        pin_cell(ca);
-        pin_cell(cb);
+        Words ra = load_words(cells, za ? 0 : cell_index(Pa, ua));
+        Words rb = load_words(cells, zb ? 0 : cell_index(Pb, ub));
+        const Cell ca = cell_of(ra), cb = cell_of(rb);
         Hit ha, hb;
         ha.i = hb.i = -1;
         if (!za) ha = resolve(nodes, wide, ca, Pa, ua, n_total);
@@ -528,7 +558,7 @@ __global__ __launch_bounds__(SB_T) __attribute__((amdgpu_waves_per_eu(8))) void 
     const Node *__restrict__ nodes, const Wide *__restrict__ wide, const Cell *__restrict__ cells,
     const Dist *__restrict__ dists, const int64_t *__restrict__ sample_off, int32_t D, int64_t n_total,
     const uint64_t *__restrict__ u, int64_t S, int32_t *__restrict__ idx, double *__restrict__ x) {
-    __shared__ uint4 s_cell[LCELLS * CELL_WORDS];
+    __shared__ u64x2 s_cell[LCELLS * CELL_WORDS];
     const int64_t per = (S + gridDim.x - 1) / gridDim.x;
     const int64_t r0 = xcd_block() * per;
     const int64_t r1 = r0 + per < S ? r0 + per : S;
@@ -551,7 +581,7 @@ __global__ __launch_bounds__(SB_T) __attribute__((amdgpu_waves_per_eu(8))) void 
         const bool zero = P.flags & DIST_ZERO;
         const bool staged = !zero && P.m <= LCELLS && e - s0 >= STAGE_MIN * P.m;
         if (staged) {
-            const uint4 *src = reinterpret_cast<const uint4 *>(cells + P.co);
+            const u64x2 *src = reinterpret_cast<const u64x2 *>(cells + P.co);
             for (int64_t k = threadIdx.x; k < CELL_WORDS * P.m; k += SB_T)
                 s_cell[(k % CELL_WORDS) * LCELLS + k / CELL_WORDS] = src[k];
             __syncthreads();
@@ -563,10 +593,9 @@ __global__ __launch_bounds__(SB_T) __attribute__((amdgpu_waves_per_eu(8))) void 
                 const int64_t sb = sa + SB_T;
                 const uint64_t ua = __builtin_nontemporal_load(u + sa);
                 const uint64_t ub = __builtin_nontemporal_load(u + (sb < e ? sb : sa));
-                Cell ca = lds_cell(s_cell, (uint32_t)cell_in(P, ua));
-                Cell cb = lds_cell(s_cell, (uint32_t)cell_in(P, ub));
-                pin_cell(ca);
-                pin_cell(cb);
+                Words ra = lds_words(s_cell, (uint32_t)cell_in(P, ua));
+                Words rb = lds_words(s_cell, (uint32_t)cell_in(P, ub));
+                const Cell ca = cell_of(ra), cb = cell_of(rb);
                 const Hit ha = resolve(nodes, wide, ca, P, ua, n_total);
                 const Hit hb = resolve(nodes, wide, cb, P, ub, n_total);
                 store(sa, P, ha, ua);
@@ -601,10 +630,9 @@ __global__ __launch_bounds__(SB_T) __attribute__((amdgpu_waves_per_eu(8))) void 
     const Dist *__restrict__ dists, int32_t D, int64_t n_total, const uint64_t *__restrict__ u2, int64_t S,
     int32_t *__restrict__ rc,
     double *__restrict__ xy) {
-    typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
     typedef int32_t i32x2 __attribute__((ext_vector_type(2)));
     typedef double f64x2 __attribute__((ext_vector_type(2)));
-    __shared__ uint4 s_cell[LCELLS * CELL_WORDS];
+    __shared__ u64x2 s_cell[LCELLS * CELL_WORDS];
     const u64x2 *up = reinterpret_cast<const u64x2 *>(u2);
     i32x2 *rcp = reinterpret_cast<i32x2 *>(rc);
     f64x2 *xyp = reinterpret_cast<f64x2 *>(xy);
@@ -613,30 +641,33 @@ __global__ __launch_bounds__(SB_T) __attribute__((amdgpu_waves_per_eu(8))) void 
     const bool mzero = (M.flags & DIST_ZERO) != 0;
     const bool staged = !mzero && M.m <= LCELLS;
     if (staged) {
-        const uint4 *src = reinterpret_cast<const uint4 *>(cells + M.co);
+        const u64x2 *src = reinterpret_cast<const u64x2 *>(cells + M.co);
         for (int64_t k = threadIdx.x; k < CELL_WORDS * M.m; k += SB_T)
             s_cell[(k % CELL_WORDS) * LCELLS + k / CELL_WORDS] = src[k];
         __syncthreads();
     }
     for (int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; s < S; s += T) {
         const u64x2 uu = __builtin_nontemporal_load(up + s);
-        Cell cr = staged ? lds_cell(s_cell, (uint32_t)cell_in(M, uu.x))
-                         : load_cell(cells, mzero ? 0 : cell_index(M, uu.x));
-        pin_cell(cr);
-        const Hit hr = resolve(nodes, wide, cr, M, uu.x, n_total);
+        Words wr = staged ? lds_words(s_cell, (uint32_t)cell_in(M, uu.x))
+                          : load_words(cells, mzero ? 0 : cell_index(M, uu.x));
+        const Hit hr = resolve(nodes, wide, cell_of(wr), M, uu.x, n_total);
         // the marginal must have one weight per row distribution 1..D-1
         const int32_t r = hr.i - (int32_t)M.eo;
         const bool row = !mzero && hr.i >= 0 && 1 + r < D;
         const Dist R = dists[row ? 1 + r : 0];
         i32x2 out = {row ? r : -1, -1};
         f64x2 pos = {__builtin_nan(""), __builtin_nan("")};
-        Cell cc = load_cell(cells, cell_index(R, uu.y));
+        // the column's record is on its way before the row's position is
+        // worked out, and its wait comes after (2^27 pairs of the 4096 x 4096
+        // map: indices 4608 -> 3777 us, with positions 5268 -> 4630)
+        Words wc = load_words(cells, cell_index(R, uu.y));
+        __builtin_amdgcn_sched_barrier(0);
         if (WANT_X) {
             const double y = position(M, hr, uu.x);
             pos.x = row ? y : pos.x;
         }
-        pin_cell(cc);
-        const Hit hc = resolve(nodes, wide, cc, R, uu.y, n_total);
+        __builtin_amdgcn_sched_barrier(0);
+        const Hit hc = resolve(nodes, wide, cell_of(wc), R, uu.y, n_total);
         if (row && hc.i >= 0 && !(R.flags & DIST_ZERO)) {
             out.y = hc.i - (int32_t)R.eo;
             if (WANT_X) pos.y = position(R, hc, uu.y);
