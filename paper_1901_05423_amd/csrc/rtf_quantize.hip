@@ -6,9 +6,12 @@
 // round-half-even, so the result is the same on every IEEE machine.
 //
 // Kernels: k_qinit clears the per-distribution maxima (kept in the low word of
-// scale[d] while the call runs), k_qmax takes the maxima with integer atomics
-// on the float bits (order-preserving for non-negative floats), k_qapply
-// writes q, k_qfinal writes the scales (for one distribution k_qapply does).
+// scale[d] while the call runs), k_qmax (one distribution: k_qmax_single)
+// takes the maxima with integer atomics on the float bits (order-preserving
+// for non-negative floats), k_qapply writes q, k_qfinal the scales (for one
+// distribution k_qapply does).  A launch costs 2 to 4.5 us of the stream
+// whatever it does, so small calls take one: k_qgroup, whose blocks own whole
+// distributions.
 #include "rtf_internal.h"
 
 namespace rtf {
@@ -236,9 +239,21 @@ __global__ __launch_bounds__(QT) void k_qmax_single(const float *__restrict__ v,
     }
 }
 
+__device__ inline double scale_from_max(float mx) { return mx > 0.0f ? 4294967295.0 / (double)mx : 0.0; }
+
+__device__ inline uint32_t quantised(float x, double s) {
+    uint32_t q = 0;
+    if (x > 0.0f && !isinf(x)) {
+        double y = rint((double)x * s);
+        y = y < 1.0 ? 1.0 : y;
+        y = y > 4294967295.0 ? 4294967295.0 : y;
+        q = (uint32_t)y;
+    }
+    return q;
+}
+
 __device__ inline double scale_of(const double *scale, int32_t d) {
-    const float mx = __uint_as_float(*reinterpret_cast<const uint32_t *>(scale + d));
-    return mx > 0.0f ? 4294967295.0 / (double)mx : 0.0;
+    return scale_from_max(__uint_as_float(*reinterpret_cast<const uint32_t *>(scale + d)));
 }
 
 // One distribution: scale[0] holds either the maximum's float bits in its low
@@ -252,8 +267,7 @@ __device__ inline double scale_single(const double *scale) {
     const uint64_t word = __hip_atomic_load(reinterpret_cast<const uint64_t *>(scale),
                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (word >> 32) return __longlong_as_double((long long)word);
-    const float mx = __uint_as_float((uint32_t)word);
-    return mx > 0.0f ? 4294967295.0 / (double)mx : 0.0;
+    return scale_from_max(__uint_as_float((uint32_t)word));
 }
 
 __global__ __launch_bounds__(QT) void k_qapply(const float *__restrict__ v,
@@ -285,29 +299,149 @@ __global__ __launch_bounds__(QT) void k_qapply(const float *__restrict__ v,
             }
             s = scale_of(scale, d);
         }
-        const float x = xs[k];
-        uint32_t q = 0;
-        if (x > 0.0f && !isinf(x)) {
-            double y = rint((double)x * s);
-            y = y < 1.0 ? 1.0 : y;
-            y = y > 4294967295.0 ? 4294967295.0 : y;
-            q = (uint32_t)y;
-        }
-        out[i] = q;
+        out[i] = quantised(xs[k], s);
     }
 }
 
 __global__ void k_qfinal(double *scale, int32_t D) {
     int32_t d = blockIdx.x * blockDim.x + threadIdx.x;
     if (d >= D) return;
-    const float mx = __uint_as_float(*reinterpret_cast<const uint32_t *>(scale + d));
-    scale[d] = mx > 0.0f ? 4294967295.0 / (double)mx : 0.0;
+    scale[d] = scale_of(scale, d);
+}
+
+// The largest weight's float bits (-0.0 counts as 0) and whether a weight is
+// negative, NaN or infinite.
+__device__ inline void take_max(float x, uint32_t &mx, bool &bad) {
+    if (!(x >= 0.0f) || isinf(x)) {
+        bad = true;
+        return;
+    }
+    const uint32_t b = __float_as_uint(x) & 0x7fffffffu;
+    mx = b > mx ? b : mx;
+}
+
+__device__ inline uint32_t wave_max(uint32_t x) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const uint32_t y = __shfl_xor(x, o, 64);
+        x = y > x ? y : x;
+    }
+    return x;
+}
+
+// Small calls in one launch.  A block of QG threads owns the `per` (1 or 16)
+// distributions from per * blockIdx.x on: with 16, each of its waves one of
+// at most 64 QI weights; every other distribution is the whole block's, one
+// after another.  Up to QI weights per thread stay in registers between the
+// maximum and the quantisation, so that they are read once.
+constexpr int QG = 1024;
+__global__ __launch_bounds__(QG) void k_qgroup(const float *__restrict__ v, const int64_t *__restrict__ off,
+                                               int32_t D, int64_t n, int per, double *scale,
+                                               uint32_t *__restrict__ out, uint32_t *status) {
+    __shared__ uint32_t s_max[QG / 64];
+    __shared__ int s_bad;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    // the range of distribution d, within [0, n] for any offsets
+    auto range = [&](int32_t d, int64_t &e0, int64_t &e1) {
+        e0 = off ? off[d] : 0;
+        e1 = off ? off[d + 1] : n;
+        e0 = e0 < 0 ? 0 : (e0 > n ? n : e0);
+        e1 = e1 < e0 ? e0 : (e1 > n ? n : e1);
+    };
+    bool bad = false;
+    if (tid == 0) s_bad = 0;
+    const int32_t d0 = (int32_t)blockIdx.x * per;
+    int64_t e0, e1;
+    if (per > 1 && d0 + w < D) {
+        range(d0 + w, e0, e1);
+        if (e1 - e0 <= 64 * QI) {
+            float xs[QI];
+            uint32_t mx = 0;
+#pragma unroll
+            for (int k = 0; k < QI; ++k) {
+                const int64_t i = e0 + lane + 64 * k;
+                xs[k] = i < e1 ? v[i] : 0.0f;
+            }
+#pragma unroll
+            for (int k = 0; k < QI; ++k) take_max(xs[k], mx, bad);
+            const double s = scale_from_max(__uint_as_float(wave_max(mx)));
+            if (lane == 0) scale[d0 + w] = s;
+#pragma unroll
+            for (int k = 0; k < QI; ++k) {
+                const int64_t i = e0 + lane + 64 * k;
+                if (i < e1) out[i] = quantised(xs[k], s);
+            }
+        }
+    }
+    for (int32_t d = d0; d < d0 + per && d < D; ++d) {
+        range(d, e0, e1);
+        const int64_t cnt = e1 - e0;
+        if (per > 1 && cnt <= 64 * QI) continue;  // a wave's
+        float xs[QI];
+        uint32_t mx = 0;
+        for (int64_t c = e0; c < e1; c += (int64_t)QG * QI) {
+#pragma unroll
+            for (int k = 0; k < QI; ++k) {
+                const int64_t i = c + tid + (int64_t)QG * k;
+                xs[k] = i < e1 ? v[i] : 0.0f;
+            }
+#pragma unroll
+            for (int k = 0; k < QI; ++k) take_max(xs[k], mx, bad);
+        }
+        mx = wave_max(mx);
+        __syncthreads();  // the previous distribution's maxima have been read
+        if (lane == 0) s_max[w] = mx;
+        __syncthreads();
+        mx = 0;
+        for (int i = 0; i < QG / 64; ++i) mx = s_max[i] > mx ? s_max[i] : mx;
+        const double s = scale_from_max(__uint_as_float(mx));
+        if (tid == 0) scale[d] = s;
+        for (int64_t c = e0; c < e1; c += (int64_t)QG * QI) {
+            if (cnt > (int64_t)QG * QI) {
+#pragma unroll
+                for (int k = 0; k < QI; ++k) {
+                    const int64_t i = c + tid + (int64_t)QG * k;
+                    xs[k] = i < e1 ? v[i] : 0.0f;
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < QI; ++k) {
+                const int64_t i = c + tid + (int64_t)QG * k;
+                if (i < e1) out[i] = quantised(xs[k], s);
+            }
+        }
+    }
+    if (!status) return;
+    __syncthreads();
+    if (bad) s_bad = 1;
+    __syncthreads();
+    if (tid == 0 && s_bad) atomicOr(status, status_bit(RTF_ERR_VALUE));
+}
+
+// The distributions per block of k_qgroup, or 0 for the kernels that cut the
+// weights evenly.  One block streams a distribution at about 10 us per 2^15
+// weights where those take 8 to 13 us in all (a graph's replay, 20 calls): one
+// distribution of 16384 weights 6.7 us against 7.7, of 32768 12.4 against
+// 7.9; 300 of 500 9.1 against 18.0, 16 of 16000 6.8 against 12.5, but two of
+// 100000 34 against 13.  The sizes are not known here, so the totals are held
+// to what a single distribution among them may cost: 2^17 weights, or 2^18
+// where the average of at most 512 sends each wave one (3000 of 10 weights
+// and one of 200000: 68 us against 118).
+int qgroup_per(int32_t D, int64_t n, bool batched) {
+    if (!batched || D == 1) return n <= 16384 ? 1 : 0;
+    if (n <= 512 * (int64_t)D) return n <= (1 << 18) ? 16 : 0;
+    return n <= (1 << 17) && n <= 16384 * (int64_t)D ? 1 : 0;
 }
 
 }  // namespace
 
 hipError_t launch_quantize(const float *v, const int64_t *elem_off, int32_t D, int64_t n_total,
                            uint32_t *out, double *scale, uint32_t *status, hipStream_t st) {
+    if (const int per = qgroup_per(D, n_total, elem_off != nullptr)) {
+        hipLaunchKernelGGL(k_qgroup, dim3((unsigned)((D + per - 1) / per)), dim3(QG), 0, st, v, elem_off, D, n_total,
+                           per, scale, out, status);
+        return hipGetLastError();
+    }
     const int db = (D + 255) / 256;
     const int64_t nb = (n_total + (int64_t)QT * QI - 1) / ((int64_t)QT * QI);
     hipLaunchKernelGGL(k_qinit, dim3(db), dim3(256), 0, st, scale, D);
