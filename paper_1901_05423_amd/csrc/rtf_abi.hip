@@ -20,16 +20,17 @@ struct Layout {
     int64_t ntiles;
 };
 
-// Per-tile arrays are sized for the smaller tile (more tiles) and the
-// deferral list for whichever tile shape needs more slots, so that one
-// workspace size serves every tile shape.
+// Per-tile arrays are sized for the smallest tile the size can be built with
+// (more tiles) and the deferral list for whichever tile shape needs more
+// slots, so that one workspace size serves every tile shape.
 int64_t ntiles_of(int64_t n, int tile) { return (n + tile - 1) / tile; }
 
 Layout make_layout(int32_t D, int64_t n, int64_t m) {
     Layout L;
-    L.ntiles = ntiles_of(n, Tile1024::TILE);
-    const int64_t defer_slots = std::max(L.ntiles * Tile1024::DEFER_CAP,
-                                         ntiles_of(n, Tile2048::TILE) * Tile2048::DEFER_CAP);
+    L.ntiles = ntiles_of(n, build_tile(D, n, Tile1024::TILE));
+    const int64_t defer_slots = std::max({ntiles_of(n, Tile512::TILE) * Tile512::DEFER_CAP,
+                                          ntiles_of(n, Tile1024::TILE) * Tile1024::DEFER_CAP,
+                                          ntiles_of(n, Tile2048::TILE) * Tile2048::DEFER_CAP});
     size_t o = 0;
     L.status = o;
     o = align256(o + 256);
@@ -109,8 +110,8 @@ rtf_status build_common(const uint32_t *w, const int64_t *elem_off, const int64_
     a.D = D;
     a.n_total = n;
     a.m_total = m;
-    a.tile = tile;
-    a.ntiles = ntiles_of(n, tile);
+    a.tile = build_tile(D, n, tile);
+    a.ntiles = ntiles_of(n, a.tile);
     a.nodes = static_cast<Node *>(f.nodes);
     a.cells = static_cast<Cell *>(f.cells);
     a.dists = static_cast<Dist *>(f.dists);

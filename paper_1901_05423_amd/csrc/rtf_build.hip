@@ -533,11 +533,17 @@ static_assert(2 * HALO == 64, "wave 0 loads both halos, one leaf per lane");
 constexpr int32_t SLOT_EMPTY = INT32_MIN;
 
 // Owner codes of the guide cells staged in the window: which local leaf a
-// cell record comes from (low 14 bits) and how (top 2 bits).
+// cell record comes from (low 14 bits) and how (top 2 bits).  The covered
+// cells of a run are not written one by one: an empty cell takes the owner of
+// the next cell to its right that holds a code, the leaf before a WIN_ROOT
+// leaf or the leaf of a WIN_TAIL.  (Written by the lane that finds the run,
+// up to RUN_CAP cells in turn, they took 10 of the 24 us a tile of 100003
+// Zipf weights needs.)
 constexpr uint16_t WIN_EMPTY = 0xFFFF;
-constexpr uint16_t WIN_ROOT = 0 << 14;  // the cell's first node
-constexpr uint16_t WIN_HEAD = 1 << 14;  // covered by the leaf before that node
-constexpr uint16_t WIN_TAIL = 2 << 14;  // covered by a distribution's last leaf
+constexpr uint16_t WIN_ROOT = 0 << 14;   // the cell's first node; covers back
+constexpr uint16_t WIN_HEAD = 1 << 14;   // covered by the leaf before the next first node
+constexpr uint16_t WIN_TAIL = 2 << 14;   // covered by a distribution's last leaf; covers back
+constexpr uint16_t WIN_ALONE = 3 << 14;  // the cell's first node; the cells before are not its own
 constexpr uint16_t WIN_KIND = 0xC000, WIN_LEAF = 0x3FFF;
 template <class T>
 struct alignas(16) TileSmem {
@@ -902,18 +908,19 @@ __global__ __launch_bounds__(T::BT) __attribute__((amdgpu_waves_per_eu(BATCHED ?
             const int32_t nc = sm.cell[li + 1];
             const bool next_same = nc >= 0 && !(sm.key[li + 1] == 0 && nc != cj);
             if (root) {
+                // the covered cells before it: a distribution's first node
+                // has none, a long run of them is listed
+                const int32_t pc = sm.cell[li - 1];
+                const int32_t run = kj != 0 ? cj - pc - 1 : 0;
+                if (run > RUN_CAP) push_run(a, pc + 1, cj, gj - 1, sm.key[li - 1], kj);
                 const int64_t x = cj - sm.c_begin;
                 if (x >= 0 && x < WIN) {
-                    sm.win[x] = (uint16_t)(WIN_ROOT | li);
+                    sm.win[x] = (uint16_t)((kj != 0 && run <= RUN_CAP ? WIN_ROOT : WIN_ALONE) | li);
                     xmax = max(xmax, (int)x);
                 } else {
                     root_cell_record(sm, a.cells, cj, li, lb0);
-                }
-                const int32_t pc = sm.cell[li - 1];
-                if (kj != 0 && cj - pc > 1) {
-                    if (cj - pc - 1 > RUN_CAP) push_run(a, pc + 1, cj, gj - 1, sm.key[li - 1], kj);
-                    else
-                        for (int64_t c = pc + 1; c < cj; ++c)
+                    if (run <= RUN_CAP)
+                        for (int64_t c = cj - run; c < cj; ++c)
                             xmax = max(xmax, put_cell(sm, a.cells, c, (uint16_t)(WIN_HEAD | li), lb0));
                 }
             }
@@ -924,7 +931,8 @@ __global__ __launch_bounds__(T::BT) __attribute__((amdgpu_waves_per_eu(BATCHED ?
                 if (cend - cj > 1) {
                     if (cend - cj - 1 > RUN_CAP) push_run(a, cj + 1, cend, gj, kj, KEY_END);
                     else
-                        for (int64_t c = cj + 1; c < cend; ++c)
+                        // in the window the last of them stands for all
+                        for (int64_t c = cend - 1 - sm.c_begin < WIN ? cend - 1 : cj + 1; c < cend; ++c)
                             xmax = max(xmax, put_cell(sm, a.cells, c, (uint16_t)(WIN_TAIL | li), lb0));
                 }
             }
@@ -939,16 +947,23 @@ __global__ __launch_bounds__(T::BT) __attribute__((amdgpu_waves_per_eu(BATCHED ?
 
     // ---- phase 5: the staged guide cells, 64 consecutive records per wave ---
     const int span = sm.win_hi + 1;
-    for (int x = tid; x < span; x += BT) {
-        const uint16_t w = sm.win[x];
-        if (w == WIN_EMPTY) continue;
+    const int lane = tid & 63;
+    for (int x0 = tid - lane; x0 < span; x0 += BT) {
+        const int x = x0 + lane;
+        uint16_t w = x < span ? sm.win[x] : WIN_EMPTY;
+        const uint16_t ahead = x + 64 < span ? sm.win[x + 64] : WIN_EMPTY;
+        // the cells with a code among this wave's 64 and the next 64
+        const uint64_t here = __ballot(w != WIN_EMPTY) >> lane, next = __ballot(ahead != WIN_EMPTY);
+        if (x >= span || (here | next) == 0) continue;
+        const bool own = w != WIN_EMPTY;
+        if (!own) w = sm.win[here ? x + __builtin_ctzll(here) : x0 + 64 + __builtin_ctzll(next)];
         const int64_t c = sm.c_begin + x;
         const int li = w & WIN_LEAF;
         const int32_t g = lb0 + li;
         const int kind = w & WIN_KIND;
-        if (kind == WIN_ROOT) root_cell_record(sm, a.cells, c, li, lb0);
-        else if (kind == WIN_HEAD) store_covered(a.cells, c, sm.key[li - 1], sm.key[li], g - 1);
-        else store_covered(a.cells, c, sm.key[li], KEY_END, g);
+        if (own && (kind == WIN_ROOT || kind == WIN_ALONE)) root_cell_record(sm, a.cells, c, li, lb0);
+        else if (kind == WIN_TAIL) store_covered(a.cells, c, sm.key[li], KEY_END, g);
+        else if (kind != WIN_ALONE) store_covered(a.cells, c, sm.key[li - 1], sm.key[li], g - 1);
     }
     // the deferred nodes join one grid-wide list (a tile with more than
     // DEFER_CAP of them is redone whole by the fix-up instead)
@@ -1577,7 +1592,8 @@ void enqueue_build(const BuildArgs &a, hipStream_t st) {
 }
 
 hipError_t launch_build(const BuildArgs &a, hipStream_t st) {
-    if (a.tile == Tile1024::TILE) enqueue_build<Tile1024>(a, st);
+    if (a.tile == Tile512::TILE) enqueue_build<Tile512>(a, st);
+    else if (a.tile == Tile1024::TILE) enqueue_build<Tile1024>(a, st);
     else enqueue_build<Tile2048>(a, st);
     return hipGetLastError();
 }

@@ -43,6 +43,17 @@ struct Tiling {
 using Tile2048 = Tiling<512, 4, 8, 6>;  // 40 KB of LDS per tile: four per CU
 using Tile1024 = Tiling<256, 4, 7, 6>;  // 21 KB: seven per CU
 constexpr int TILE_DEFAULT = Tile2048::TILE;
+// Small builds take 512-element tiles whatever tile was asked for: they leave
+// CUs idle otherwise, and a tile's time is its own latency.  Build alone, at
+// 2048, 1024 and 512 elements: 100003 Zipf weights 33, 32 and 30 us, 2^20 of
+// them 55, 57 and 49, 2^21 uniform ones 38.5, 37.9 and 38.6; 300 distributions
+// of 500 28, 25 and 21, 1000 of 700 58, 51 and 49, 256 of 4096 34, 32 and 33.
+using Tile512 = Tiling<256, 2, 4, 4>;
+// The elements per tile of a build of D distributions and n weights in all,
+// with the tile asked for.
+constexpr int build_tile(int32_t D, int64_t n, int tile) {
+    return n <= (D > 1 ? (int64_t)3 << 18 : (int64_t)1 << 20) ? Tile512::TILE : tile;
+}
 // Leaves on either side of a tile whose keys are recomputed locally so that
 // subtree scans near the tile edges stay in LDS.
 constexpr int HALO = 32;
@@ -142,7 +153,7 @@ struct BuildArgs {
     int32_t D;
     int64_t n_total;
     int64_t m_total;
-    int32_t tile;                 // elements per tile: Tile2048::TILE or Tile1024::TILE
+    int32_t tile;                 // elements per tile, of the shapes above
     int64_t ntiles;
     Node *nodes;
     Cell *cells;

@@ -429,7 +429,7 @@ __global__ __launch_bounds__(QG) void k_qgroup(const float *__restrict__ v, cons
 // and one of 200000: 68 us against 118).
 int qgroup_per(int32_t D, int64_t n, bool batched) {
     if (!batched || D == 1) return n <= 16384 ? 1 : 0;
-    if (n <= 512 * (int64_t)D) return n <= (1 << 18) ? 16 : 0;
+    if (n <= 512 * (int64_t)D) return n <= (1 << 18) ? (D > 1024 ? 16 : 1) : 0;
     return n <= (1 << 17) && n <= 16384 * (int64_t)D ? 1 : 0;
 }
 
