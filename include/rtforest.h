@@ -89,7 +89,7 @@ typedef enum rtf_status {
  */
 typedef struct rtf_forest {
     int32_t D;          /* number of distributions */
-    int32_t tile;       /* elements per build tile */
+    int32_t tile;       /* elements per build tile asked for */
     int64_t n_total;    /* leaves = nodes over all distributions */
     int64_t m_total;    /* guide cells over all distributions */
     void *nodes;        /* device: n_total node records */
@@ -161,7 +161,8 @@ rtf_status rtf_build_batched(const uint32_t *w, const int64_t *elem_off,
  * The forest is the same for either tile, bit for bit; only the speed
  * differs (1024-element tiles suit batches of many small distributions).
  * The workspace sizes above cover both tiles.  The descriptor's tile field
- * records the choice.
+ * records the choice; builds of up to 2^20 weights (3 2^18 in a batch) are
+ * cut finer than either.
  */
 rtf_status rtf_build_tiled(const uint32_t *w, int64_t n, int64_t m, int32_t tile,
                            void *ws, size_t ws_bytes, hipStream_t stream,

@@ -49,6 +49,12 @@ constexpr int TILE_DEFAULT = Tile2048::TILE;
 // them 55, 57 and 49, 2^21 uniform ones 38.5, 37.9 and 38.6; 300 distributions
 // of 500 28, 25 and 21, 1000 of 700 58, 51 and 49, 256 of 4096 34, 32 and 33.
 using Tile512 = Tiling<256, 2, 4, 4>;
+// One distribution in a single launch: a tile holds all of it.  The kernel
+// alone takes what the three launches it replaces do (1000 weights 15.7 us
+// against 15.3, 2048 18.3 against 15.2 in a graph); what it saves is their
+// enqueueing (quantise, build and sample 1024 weights: 39.9 -> 33.4 us a call).
+using TileAlone = Tiling<1024, 2, 4, 4>;
+constexpr int64_t ALONE_CELLS = 4096;  // its block fills the long runs too
 // The elements per tile of a build of D distributions and n weights in all,
 // with the tile asked for.
 constexpr int build_tile(int32_t D, int64_t n, int tile) {
