@@ -46,7 +46,12 @@ constexpr int64_t STAGE_SEGMENT = 4096;
 // quads; index only 1339 and 1351).
 constexpr int64_t QUAD_TABLE = 12 << 20;
 
-constexpr int SCHUNK = 256 * 8;  // samples per block step of the batched kernel
+// The batched kernel's blocks take chunks of 2048 samples from 2^21 samples
+// on, below that 512, so that small calls reach more CUs (137K samples of 333
+// distributions 14.6 us in chunks of 2048, 7.4 of 512; 2^20 of 2000 21.6 and
+// 18.8; but 5.1M of 10000 144 and 152: a chunk's search for its distributions
+// is paid four times as often).
+constexpr int64_t CHUNK_LONG = 1 << 21;
 constexpr int CHUNK_DISTS = 256;  // distributions a chunk can stage in LDS
 
 static_assert(sizeof(Dist) == 64, "a staged record is four 16-byte words");
@@ -410,7 +415,7 @@ __global__ __launch_bounds__(256) void k_sample(const Node *__restrict__ nodes,
                                                 int32_t D, int64_t n_total,
                                                 const uint64_t *__restrict__ u, int64_t S,
                                                 int32_t *__restrict__ idx,
-                                                double *__restrict__ x) {
+                                                double *__restrict__ x, int64_t chunk) {
     if (!BATCHED) {
         const Dist P = dists[0];
         const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -459,7 +464,7 @@ __global__ __launch_bounds__(256) void k_sample(const Node *__restrict__ nodes,
     }
     __shared__ int64_t s_soff[256];
     __shared__ uint4 s_dist[4 * CHUNK_DISTS];
-    // batched: a block takes chunks of SCHUNK consecutive samples (numbered
+    // batched: a block takes chunks of consecutive samples (numbered
     // per XCD, so that one XCD's L2 serves a few neighbouring distributions),
     // finds the chunk's first distribution once (block-wide), and each lane
     // steps on through the few distributions the chunk spans, two samples
@@ -490,15 +495,16 @@ __global__ __launch_bounds__(256) void k_sample(const Node *__restrict__ nodes,
         store(sa, Pa, ha, ua);
         if (has_b) store(sb, Pb, hb, ub);
     };
-    for (int64_t c0 = xcd_block() * SCHUNK; c0 < S; c0 += (int64_t)gridDim.x * SCHUNK) {
+    for (int64_t c0 = xcd_block() * chunk; c0 < S; c0 += (int64_t)gridDim.x * chunk) {
         int32_t d = __builtin_amdgcn_readfirstlane(block_find_segment(sample_off, D, c0));
         int64_t dend = sample_off[d + 1];
-        const int64_t cend = c0 + SCHUNK < S ? c0 + SCHUNK : S;
+        const int64_t cend = c0 + chunk < S ? c0 + chunk : S;
+        const int steps = (int)(chunk / 256);
         if (dend >= cend) {
             // the chunk lies in one distribution: its parameters are uniform
             const Dist P = dists[d];
-#pragma unroll
-            for (int k = 0; k < SCHUNK / 256; k += 2) {
+#pragma unroll 1
+            for (int k = 0; k < steps; k += 2) {
                 const int64_t sa = c0 + threadIdx.x + 256 * k, sb = sa + 256;
                 if (sa >= cend) break;
                 two(sa, sb, sb < cend, P, P);
@@ -517,8 +523,8 @@ __global__ __launch_bounds__(256) void k_sample(const Node *__restrict__ nodes,
             const uint4 *src = reinterpret_cast<const uint4 *>(dists + d);
             for (int q = threadIdx.x; q < 4 * (nb + 1); q += 256) s_dist[q] = src[q];
             __syncthreads();
-#pragma unroll
-            for (int k = 0; k < SCHUNK / 256; k += 2) {
+#pragma unroll 1
+            for (int k = 0; k < steps; k += 2) {
                 const int64_t sa = c0 + threadIdx.x + 256 * k, sb = sa + 256;
                 if (sa >= cend) break;
                 const bool has_b = sb < cend;
@@ -529,14 +535,14 @@ __global__ __launch_bounds__(256) void k_sample(const Node *__restrict__ nodes,
             __syncthreads();  // before the next chunk restages
             continue;
         }
-#pragma unroll
-        for (int k = 0; k < SCHUNK / 256; k += 2) {
+#pragma unroll 1
+        for (int k = 0; k < steps; k += 2) {
             const int64_t sa = c0 + threadIdx.x + 256 * k, sb = sa + 256;
-            if (sa >= S) break;
+            if (sa >= cend) break;
             // (d stays below D even for offsets that break the rules)
             while (sa >= dend && d + 1 < D) dend = sample_off[++d + 1];
             const int32_t da = d;
-            const bool has_b = sb < S;
+            const bool has_b = sb < cend;
             if (has_b)
                 while (sb >= dend && d + 1 < D) dend = sample_off[++d + 1];
             two(sa, sb, has_b, dists[da], dists[d]);
@@ -759,9 +765,10 @@ hipError_t launch_sample(const Node *nodes, const Wide *wide, const Cell *cells,
                                dists, sample_off, D, n_total, u, S, idx, x);
         return hipGetLastError();
     }
-    const dim3 g(batched ? grid_for((S + SCHUNK / 256 - 1) / (SCHUNK / 256)) : grid_for(S)), b(256);
+    const int64_t chunk = S >= CHUNK_LONG ? 2048 : 512;
+    const dim3 g(batched ? grid_for((S + chunk / 256 - 1) / (chunk / 256)) : grid_for(S)), b(256);
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, g, b, 0, st, nodes, wide, cells, dists, sample_off, D, n_total, u, S, idx, x);
+        hipLaunchKernelGGL(kernel, g, b, 0, st, nodes, wide, cells, dists, sample_off, D, n_total, u, S, idx, x, chunk);
     };
     if (batched) {
         if (x) go(k_sample<true, true, false>);
