@@ -126,54 +126,42 @@ __device__ inline Cell cell_of(Words &r) {
     return c;
 }
 
-// One 4x4 transposition step inside every quad of lanes: out0 takes a from
-// the lane itself where `odd` is clear and b from the partner lane (the DPP
-// quad permutation CTRL) where it is set; out1 the other way round.
-template <int CTRL>
-__device__ inline void quad_swap(uint32_t &a, uint32_t &b, bool odd) {
-    const uint32_t pa = (uint32_t)__builtin_amdgcn_mov_dpp((int)a, CTRL, 0xf, 0xf, true);
-    const uint32_t pb = (uint32_t)__builtin_amdgcn_mov_dpp((int)b, CTRL, 0xf, 0xf, true);
-    const uint32_t o0 = odd ? pb : a, o1 = odd ? b : pa;
-    a = o0;
-    b = o1;
-}
-template <int CTRL>
-__device__ inline void quad_swap4(uint4 &a, uint4 &b, bool odd) {
-    quad_swap<CTRL>(a.x, b.x, odd);
-    quad_swap<CTRL>(a.y, b.y, odd);
-    quad_swap<CTRL>(a.z, b.z, odd);
-    quad_swap<CTRL>(a.w, b.w, odd);
+// Keeps the compiler from moving a wave's LDS accesses across: within a wave
+// they execute in order, so lanes may hand each other data without a barrier.
+__device__ inline void wave_fence() {
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
 }
 
-// Every lane's record cells[g], fetched by whole quads of lanes: in
-// step q the four lanes of a quad load the four 16-byte words of lane q's
-// record, so that a wave instruction touches 16 lines instead of 64, and a
-// 4x4 transposition inside the quads hands every lane its own words.  All
-// lanes of a quad must call it together.
-__device__ inline Words load_words_quad(const Cell *cells, uint32_t g) {
+// Every lane's record cells[g], fetched by whole quads of lanes: in step q the
+// four lanes of a quad load the four 16-byte words of lane q's record, so that
+// a wave instruction touches 16 lines instead of 64, and the words go through
+// the wave's part of LDS to the lane they belong to.  A record takes five
+// 16-byte slots there, which spreads both the writes and the reads over all
+// banks.  (A transposition by DPP moves takes 64 vector instructions a record:
+// 2^26 samples with x from a 16 KiB table 586 us against 561, indices 405
+// against 387.)  All lanes of the wave must call it together; the table is at
+// most 4 GiB.
+constexpr int QUAD_SLOTS = 64 * (CELL_WORDS + 1);  // 16-byte slots per wave
+__device__ inline Words load_words_quad(const Cell *cells, uint32_t g, u64x2 *s_wave) {
     static_assert(CELL_WORDS == 4, "one word of a record per lane of a quad");
-    uint4 v[CELL_WORDS];
-    const uint32_t lane = threadIdx.x;
-    const char *p = reinterpret_cast<const char *>(cells) + 16 * (lane & 3);
-    const uint32_t g0 = (uint32_t)__builtin_amdgcn_mov_dpp((int)g, 0x00, 0xf, 0xf, true);
-    const uint32_t g1 = (uint32_t)__builtin_amdgcn_mov_dpp((int)g, 0x55, 0xf, 0xf, true);
-    const uint32_t g2 = (uint32_t)__builtin_amdgcn_mov_dpp((int)g, 0xaa, 0xf, 0xf, true);
-    const uint32_t g3 = (uint32_t)__builtin_amdgcn_mov_dpp((int)g, 0xff, 0xf, 0xf, true);
-    v[0] = *reinterpret_cast<const uint4 *>(p + ((uint64_t)g0 << 6));
-    v[1] = *reinterpret_cast<const uint4 *>(p + ((uint64_t)g1 << 6));
-    v[2] = *reinterpret_cast<const uint4 *>(p + ((uint64_t)g2 << 6));
-    v[3] = *reinterpret_cast<const uint4 *>(p + ((uint64_t)g3 << 6));
-    const bool o1 = lane & 1, o2 = lane & 2;
-    quad_swap4<0xb1>(v[0], v[1], o1);  // quad_perm 1 0 3 2
-    quad_swap4<0xb1>(v[2], v[3], o1);
-    quad_swap4<0x4e>(v[0], v[2], o2);  // quad_perm 2 3 0 1
-    quad_swap4<0x4e>(v[1], v[3], o2);
-    Words r;
+    const uint32_t lane = threadIdx.x & 63, w = lane & 3;
+    const char *base = reinterpret_cast<const char *>(cells);
+    const int off = (int)(g << 6);
+    u64x2 v[CELL_WORDS];
+    v[0] = *reinterpret_cast<const u64x2 *>(base + ((uint32_t)__builtin_amdgcn_mov_dpp(off, 0x00, 0xf, 0xf, true) + 16 * w));
+    v[1] = *reinterpret_cast<const u64x2 *>(base + ((uint32_t)__builtin_amdgcn_mov_dpp(off, 0x55, 0xf, 0xf, true) + 16 * w));
+    v[2] = *reinterpret_cast<const u64x2 *>(base + ((uint32_t)__builtin_amdgcn_mov_dpp(off, 0xaa, 0xf, 0xf, true) + 16 * w));
+    v[3] = *reinterpret_cast<const u64x2 *>(base + ((uint32_t)__builtin_amdgcn_mov_dpp(off, 0xff, 0xf, 0xf, true) + 16 * w));
+    u64x2 *to = s_wave + (lane & ~3u) * (CELL_WORDS + 1) + w;
 #pragma unroll
-    for (int w = 0; w < CELL_WORDS; ++w) {
-        r.v[w].x = ((uint64_t)v[w].y << 32) | v[w].x;
-        r.v[w].y = ((uint64_t)v[w].w << 32) | v[w].z;
-    }
+    for (int q = 0; q < 4; ++q) to[q * (CELL_WORDS + 1)] = v[q];
+    wave_fence();
+    Words r;
+    const u64x2 *from = s_wave + lane * (CELL_WORDS + 1);
+#pragma unroll
+    for (int q = 0; q < CELL_WORDS; ++q) r.v[q] = from[q];
+    wave_fence();
     return r;
 }
 
@@ -417,12 +405,14 @@ __global__ __launch_bounds__(256) void k_sample(const Node *__restrict__ nodes,
                                                 int32_t *__restrict__ idx,
                                                 double *__restrict__ x, int64_t chunk) {
     if (!BATCHED) {
+        __shared__ u64x2 s_quad[QUAD ? 4 * QUAD_SLOTS : 1];
+        u64x2 *s_wave = s_quad + (QUAD ? (threadIdx.x >> 6) * QUAD_SLOTS : 0);
         const Dist P = dists[0];
         const int64_t stride = (int64_t)gridDim.x * blockDim.x;
         auto sample = [&](uint64_t us) {
             const int64_t g = cell_in(P, us);
             Words r;
-            if (QUAD && !narrow_wave((uint32_t)g)) r = load_words_quad(cells, (uint32_t)g);
+            if (QUAD && !narrow_wave((uint32_t)g)) r = load_words_quad(cells, (uint32_t)g, s_wave);
             else r = load_words(cells, g);
             return resolve(nodes, wide, cell_of(r), P, us, n_total);
         };
@@ -750,7 +740,7 @@ hipError_t launch_sample(const Node *nodes, const Wide *wide, const Cell *cells,
                          const int64_t *sample_off, int32_t D, int64_t n_total, int64_t m_total,
                          const uint64_t *u, int64_t S, int32_t *idx, double *x,
                          hipStream_t st) {
-    const bool batched = sample_off != nullptr;
+    const bool batched = sample_off != nullptr && D > 1;  // one distribution's samples are all its own
     // many samples per cell and per distribution, and small distributions:
     // stage the cells in LDS (two blocks of SB_T threads per CU)
     if (batched && S >= (int64_t)STAGE_MIN * m_total && S >= STAGE_SEGMENT * D &&
