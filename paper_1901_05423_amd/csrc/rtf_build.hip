@@ -169,7 +169,7 @@ __device__ inline int32_t cell_of_key(uint64_t key, const Dist &P) {
 __device__ inline Leaf make_leaf(uint64_t C, const Dist &P) {
     Leaf L;
     if (C < P.W) {
-        L.key = fixed_point_key(C, P.W << P.s, P.v, P.s);
+        L.key = P.s >= 2 ? fixed_point_key_62(C, P.W, P.v, P.s) : fixed_point_key(C, P.W << P.s, P.v, P.s);
         L.cell = cell_of_key(L.key, P);
     } else {
         L.key = ~0ull;

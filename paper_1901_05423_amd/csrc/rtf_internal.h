@@ -216,11 +216,27 @@ __host__ __device__ inline uint64_t reciprocal_2by1(uint64_t d) {
     return v;
 }
 
+// Key U = ceil(C * 2^64 / W) for 0 <= C < W < 2^62, given s = clz(W) and
+// v = reciprocal_2by1(W << s).  q = floor(u1 (2^64 + v) / 2^64), u1 = C << s,
+// is the quotient's floor or one below it, since 2^64 + v falls short of
+// 2^128 / (W << s) by less than one.  The remainder C 2^64 - q W then lies in
+// [0, 2 W), below 2^63, so its low word p' = -(q W) is all of it, and U is q
+// plus one where p' is not 0, plus another where p' > W, that is where
+// p = q W (its low word) is below 2^64 - W.
+__host__ __device__ inline uint64_t fixed_point_key_62(uint64_t C, uint64_t W, uint64_t v, uint32_t s) {
+    const uint64_t u1 = C << s;
+    const uint64_t q = u1 + mulhi64(v, u1);
+    const uint64_t p = q * W;
+    return q + (p != 0 ? (p < 0 - W ? 2 : 1) : 0);
+}
+
 // Key U = ceil(C * 2^64 / W) for 0 <= C < W, given s = clz(W), d = W << s
-// and v = reciprocal_2by1(d): one 2-by-1 division (Moller-Granlund, Alg. 4)
-// of (C << s) * 2^64 by d, then rounding up on a non-zero remainder.
+// and v = reciprocal_2by1(d): for the largest W one 2-by-1 division
+// (Moller-Granlund, Alg. 4) of (C << s) * 2^64 by d, then rounding up on a
+// non-zero remainder.
 __host__ __device__ inline uint64_t fixed_point_key(uint64_t C, uint64_t d, uint64_t v,
                                                      uint32_t s) {
+    if (s >= 2) return fixed_point_key_62(C, d >> s, v, s);
     uint64_t u1 = C << s;  // < d
     uint64_t q0 = v * u1;
     uint64_t q1 = mulhi64(v, u1) + u1 + 1;
