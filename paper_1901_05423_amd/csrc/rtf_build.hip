@@ -566,7 +566,9 @@ struct alignas(16) TileSmem {
     int32_t cell[LEAF_N];
     int16_t slot[2 * T::TILE];  // child slots of the tile's own nodes (local node index)
     uint16_t win[T::WIN];       // owner codes of cells c_begin .. c_begin + WIN - 1
-    uint64_t lvl8[LEAF_N / 8];
+    uint64_t lvl_pad0;          // SENT on either side of the levels: phase 3 reads
+    uint64_t lvl8[LEAF_N / 8];  // two 32-bit words to both sides of its own
+    uint64_t lvl_pad1;
     uint64_t wave[T::BT / 64];
     uint64_t own[2 * T::BT / 64];
     int64_t c_begin;
@@ -637,6 +639,59 @@ template <class T>
 __device__ inline void link(TileSmem<T> &sm, int pn, int side, int child) {
     const int s = pn - HALO;
     if (s >= 0 && s < T::TILE) sm.slot[2 * s + side] = (int16_t)child;
+}
+
+// the 32-bit level words g - 2 .. g + 2
+template <class T>
+__device__ inline void load_levels(const TileSmem<T> &sm, int g, uint32_t (&W)[5]) {
+    const uint32_t *w = reinterpret_cast<const uint32_t *>(&sm.lvl_pad0) + g;
+#pragma unroll
+    for (int k = 0; k < 5; ++k) W[k] = w[k];
+}
+
+// Boundary bi = 4 g + q of phase 3, with the twenty levels around it: writes
+// itself into its parent's slot.  A bound found in the padding lies outside
+// [0, LVL_N) and links nothing.
+template <class T>
+__device__ inline void link_boundary(TileSmem<T> &sm, int g, int q, const uint32_t (&W)[5]) {
+    constexpr int LVL_N = TileSmem<T>::LVL_N;
+    const int bi = 4 * g + q;
+    const int l = (int)((W[2] >> (8 * q)) & 0xff);
+    const bool active = l < SENT;  // (the bytes past the last boundary hold SENT)
+    // L: nearest boundary left of bi with a level above l
+    const uint32_t tl = __builtin_amdgcn_perm(0u, (uint32_t)(127 - l), 0u);
+    const uint32_t m2 = ((W[2] + tl) & 0x80808080u) & ((1u << (8 * q)) - 1u);
+    const uint32_t m1 = (W[1] + tl) & 0x80808080u;
+    const uint32_t m0 = (W[0] + tl) & 0x80808080u;
+    const uint32_t mL = m2 ? m2 : (m1 ? m1 : m0);
+    const uint32_t wL = m2 ? W[2] : (m1 ? W[1] : W[0]);
+    const int kL = m2 ? 2 : (m1 ? 1 : 0);
+    const int pL = (31 - __builtin_clz(mL | 0x80u)) >> 3;
+    int L = 4 * (g - 2 + kL) + pL;
+    int lL = (int)((wL >> (8 * pL)) & 0xff);
+    // R: nearest boundary right of bi with a level at least l
+    const uint32_t tr = __builtin_amdgcn_perm(0u, (uint32_t)(128 - l), 0u);
+    const uint32_t r2 = q < 3 ? ((W[2] + tr) & 0x80808080u) & (~0u << (8 * q + 8)) : 0u;
+    const uint32_t r3 = (W[3] + tr) & 0x80808080u;
+    const uint32_t r4 = (W[4] + tr) & 0x80808080u;
+    const uint32_t mR = r2 ? r2 : (r3 ? r3 : r4);
+    const uint32_t wR = r2 ? W[2] : (r3 ? W[3] : W[4]);
+    const int kR = r2 ? 2 : (r3 ? 3 : 4);
+    const int pR = __builtin_ctz(mR | 0x80000000u) >> 3;
+    int R = 4 * (g - 2 + kR) + pR;
+    int lR = (int)((wR >> (8 * pR)) & 0xff);
+    if (active && mL == 0) {  // wider subtree: scan on left of the window
+        L = nearest_ge_left(sm, 4 * (g - 2) - 1, l + 1);
+        lL = L >= 0 ? lvl_at(sm, L) : 0;
+    }
+    if (active && mR == 0) {  // and right of it
+        R = nearest_ge_right(sm, 4 * (g + 3), l);
+        lR = R >= 0 ? lvl_at(sm, R) : 0;
+    }
+    if (active && L >= 0 && (uint32_t)R < (uint32_t)LVL_N) {  // else the fix-up finds the parent
+        if (lL > lR) link(sm, R + 1, 0, bi + 1);
+        else link(sm, L + 1, 1, bi + 1);
+    }
 }
 
 // child slot k as a global reference (SLOT_EMPTY when nothing was linked)
@@ -898,6 +953,7 @@ __global__ __launch_bounds__(T::BT) __attribute__((amdgpu_waves_per_eu(BATCHED ?
         for (int x = tid; x < WIN / 8; x += BT) reinterpret_cast<int4 *>(sm.win)[x] = ones;
     }
     if (tid == 0) {
+        sm.lvl_pad0 = sm.lvl_pad1 = (uint64_t)SENT * 0x0101010101010101ull;
         // first guide cell whose record comes from a leaf of this tile
         const int32_t c = sm.cell[HALO], cp = sm.cell[HALO - 1];
         int64_t cb;
@@ -921,58 +977,22 @@ __global__ __launch_bounds__(T::BT) __attribute__((amdgpu_waves_per_eu(BATCHED ?
     // compares and selects, without branches; only a subtree wider than the
     // window scans on in LDS.
     {
-        const uint32_t *lv32 = reinterpret_cast<const uint32_t *>(sm.lvl8);
-        constexpr int NW32 = LEAF_N / 4;  // 32-bit level words
-        for (int g = tid; g < NW32; g += BT) {
+        for (int g = tid; g < TILE / 4; g += BT) {
             uint32_t W[5];
-            bool V[5];  // word inside the tile's level array
+            load_levels(sm, HALO / 4 + g, W);
 #pragma unroll
-            for (int k = 0; k < 5; ++k) {
-                const int gi = g - 2 + k;
-                V[k] = gi >= 0 && gi < NW32;
-                W[k] = V[k] ? lv32[gi] : 0u;
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int bi = 4 * g + q;
-                const int l = (int)((W[2] >> (8 * q)) & 0xff);
-                const bool active = bi < LVL_N && l < SENT;
-                // L: nearest boundary left of bi with a level above l
-                const uint32_t tl = __builtin_amdgcn_perm(0u, (uint32_t)(127 - l), 0u);
-                const uint32_t m2 = ((W[2] + tl) & 0x80808080u) & ((1u << (8 * q)) - 1u);
-                const uint32_t m1 = V[1] ? (W[1] + tl) & 0x80808080u : 0u;
-                const uint32_t m0 = V[0] ? (W[0] + tl) & 0x80808080u : 0u;
-                const uint32_t mL = m2 ? m2 : (m1 ? m1 : m0);
-                const uint32_t wL = m2 ? W[2] : (m1 ? W[1] : W[0]);
-                const int kL = m2 ? 2 : (m1 ? 1 : 0);
-                const int pL = (31 - __builtin_clz(mL | 0x80u)) >> 3;
-                int L = 4 * (g - 2 + kL) + pL;
-                int lL = (int)((wL >> (8 * pL)) & 0xff);
-                // R: nearest boundary right of bi with a level at least l
-                const uint32_t tr = __builtin_amdgcn_perm(0u, (uint32_t)(128 - l), 0u);
-                const uint32_t r2 = q < 3 ? ((W[2] + tr) & 0x80808080u) & (~0u << (8 * q + 8)) : 0u;
-                const uint32_t r3 = V[3] ? (W[3] + tr) & 0x80808080u : 0u;
-                const uint32_t r4 = V[4] ? (W[4] + tr) & 0x80808080u : 0u;
-                const uint32_t mR = r2 ? r2 : (r3 ? r3 : r4);
-                const uint32_t wR = r2 ? W[2] : (r3 ? W[3] : W[4]);
-                const int kR = r2 ? 2 : (r3 ? 3 : 4);
-                const int pR = __builtin_ctz(mR | 0x80000000u) >> 3;
-                int R = 4 * (g - 2 + kR) + pR;
-                int lR = (int)((wR >> (8 * pR)) & 0xff);
-                if (active && mL == 0) {  // wider subtree: scan on left of the window
-                    L = nearest_ge_left(sm, 4 * (g - 2) - 1, l + 1);
-                    lL = L >= 0 ? lvl_at(sm, L) : 0;
-                }
-                if (active && mR == 0) {  // and right of it
-                    R = nearest_ge_right(sm, 4 * (g + 3), l);
-                    lR = R >= 0 ? lvl_at(sm, R) : 0;
-                }
-                if (R >= LVL_N) R = -1;  // the padding byte: beyond the window
-                if (active && L >= 0 && R >= 0) {  // else the fix-up finds the parent
-                    if (lL > lR) link(sm, R + 1, 0, bi + 1);
-                    else link(sm, L + 1, 1, bi + 1);
-                }
-            }
+            for (int q = 0; q < 4; ++q) link_boundary(sm, HALO / 4 + g, q, W);
+        }
+        // the two halos, 64 boundaries, one per lane of the last wave: as 16
+        // words they cost one wave a whole pass.  The VALU bounds the kernel;
+        // with the words next to the array padded instead of masked, building
+        // 2^24 leaves takes 160 us (168 before), 10,000 tables 898 (936).
+        if (tid >= BT - 64) {
+            const int h = tid - (BT - 64);
+            const int bi = h < HALO ? h : TILE + h;
+            uint32_t W[5];
+            load_levels(sm, bi >> 2, W);
+            link_boundary(sm, bi >> 2, bi & 3, W);
         }
     }
     __syncthreads();
