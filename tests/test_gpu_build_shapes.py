@@ -55,6 +55,25 @@ def test_batched_rule(rtf, orc, extra, tile):  # noqa: F811
     check_batched(rtf, orc, ws, cells, [200] * len(sizes), seed=5 + extra, tile=tile)
 
 
+@pytest.mark.parametrize("D", [1, 3, 1100])
+@pytest.mark.parametrize("tiles,over", [(2048, 0), (2048, 1), (4097, 5)])
+def test_scan_blocks(rtf, orc, tiles, over, D):  # noqa: F811
+    """tile sums scanned by one block, two and three, with an odd number of
+    them and with the parameters in the same launch or the next"""
+    note(f"scan blocks tiles={tiles} over={over} D={D}")
+    rng = np.random.default_rng(tiles + over + D)
+    n = tiles * 1024 + over
+    if D == 1:
+        f = rtf.build(to_dev(w := weights(rng, n, "skew")), n // 4, tile=1024)
+        f.check()
+        assert_forest(f, orc.forest(w, m=n // 4), f"n={n}")
+        return
+    sizes = [n // D] * (D - 1)
+    sizes.append(n - sum(sizes))
+    check_batched(rtf, orc, [weights(rng, k, "skew") for k in sizes], [max(1, k // 4) for k in sizes],
+                  [50] * D, seed=tiles + D, tile=1024)
+
+
 def test_all_zero_small(rtf):  # noqa: F811
     note("all zero small")
     for n in (1, 2048, 3000):
