@@ -18,7 +18,7 @@
 //                  starts); block 0 copies the offsets into the workspace and
 //                  clears the status word and the run list
 //   k_dist_params  scan of tile sums; per distribution W, reciprocal, G0
-//   k_dist_finish  the latter for more than PT distributions
+//   k_dist_finish  the latter for more than PT distributions or SCAN_TILES tiles
 //   k_build_tile   keys, levels, node records, guide-table entries per tile
 //   k_fixup        deferred node records and long guide-table runs
 #include "rtf_internal.h"
@@ -534,7 +534,7 @@ __global__ __launch_bounds__(256) void k_dist_finish(BuildArgs a) {
 // ---------------------------------------------------------------------------
 static_assert(2 * HALO == 64, "wave 0 loads both halos, one leaf per lane");
 // Child slots hold local node indices (16 bits) and window entries 16-bit
-// owner codes, so that the tile's LDS (about 38 KB) lets four blocks share a
+// owner codes, so that the tile's LDS (40 KB) lets four blocks share a
 // CU.
 // An empty child slot holds -1 in LDS and reads as SLOT_EMPTY, never a node
 // or leaf reference.
