@@ -420,7 +420,7 @@ __global__ __launch_bounds__(T::BT) void k_tile_sums(BuildArgs a, bool vec) {
 // reads, 8 bytes per earlier sum and block, come from L2).  A batch of more
 // than one block or of more than PT distributions leaves the parameters to
 // k_dist_finish, one thread each over many blocks.  One block that scanned
-// eight sums per thread, its stores 64 bytes apart, took 55 us for 20,000
+// eight sums per thread, its stores 64 bytes apart, took 55 us for 77,700
 // tiles: that build is 852 us in all (893 before), 2^24 leaves 157 (159).
 // ---------------------------------------------------------------------------
 constexpr int PT = 1024, SCAN_TILES = 2 * PT;
