@@ -341,10 +341,12 @@ __global__ __launch_bounds__(QG) void k_qgroup(const float *__restrict__ v, cons
     __shared__ uint32_t s_max[QG / 64];
     __shared__ int s_bad;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    // the range of distribution d, within [0, n] for any offsets
+    // the range of distribution d, within [0, n] for any offsets; the first
+    // one starts at 0 and the last ends at n whatever the offsets say (as in
+    // k_qmax and k_qapply), so that every element is some distribution's
     auto range = [&](int32_t d, int64_t &e0, int64_t &e1) {
-        e0 = off ? off[d] : 0;
-        e1 = off ? off[d + 1] : n;
+        e0 = off && d > 0 ? off[d] : 0;
+        e1 = off && d + 1 < D ? off[d + 1] : n;
         e0 = e0 < 0 ? 0 : (e0 > n ? n : e0);
         e1 = e1 < e0 ? e0 : (e1 > n ? n : e1);
     };

@@ -62,3 +62,17 @@ def test_quantize_group_refuses(rtf, sizes, bad):
     status = to_dev(np.zeros(1, np.int32))
     rtf.quantize(to_dev(v), to_dev(eo) if len(sizes) > 1 else None, status=status)
     assert int(status.item()) == 1 << rtf.RTF_ERR_VALUE
+
+
+@pytest.mark.parametrize("sizes", [(20, 2000, 30), (40000, 2, 50), (5,) * 1100])
+def test_quantize_group_outer_offsets(rtf, orc, sizes):
+    """offsets that do not reach 0 and n (the build refuses them): the first
+    and the last distribution take the elements left over"""
+    note(f"quantize group outer offsets D={len(sizes)}")
+    v = weights(np.random.default_rng(len(sizes)), sum(sizes))
+    eo = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    short = eo.copy()
+    short[0], short[-1] = 3, eo[-1] - 2
+    q_ref, s_ref = orc.quantize(v, eo)
+    q, s = rtf.quantize(to_dev(v), to_dev(short))
+    assert np.array_equal(q.cpu().numpy(), q_ref) and np.array_equal(s.cpu().numpy(), s_ref)
