@@ -634,22 +634,30 @@ __global__ __launch_bounds__(SB_T) __attribute__((amdgpu_waves_per_eu(8))) void 
     f64x2 *xyp = reinterpret_cast<f64x2 *>(xy);
     const int64_t T = (int64_t)gridDim.x * blockDim.x;
     const Dist M = dists[0];
-    const bool mzero = (M.flags & DIST_ZERO) != 0;
-    const bool staged = !mzero && M.m <= LCELLS;
+    const int64_t s_first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (M.flags & DIST_ZERO) {  // a marginal without mass: no row, and none of its records was written
+        const i32x2 none = {-1, -1};
+        const f64x2 nans = {__builtin_nan(""), __builtin_nan("")};
+        for (int64_t s = s_first; s < S; s += T) {
+            rcp[s] = none;
+            if (WANT_X) xyp[s] = nans;
+        }
+        return;
+    }
+    const bool staged = M.m <= LCELLS;
     if (staged) {
         const u64x2 *src = reinterpret_cast<const u64x2 *>(cells + M.co);
         for (int64_t k = threadIdx.x; k < CELL_WORDS * M.m; k += SB_T)
             s_cell[(k % CELL_WORDS) * LCELLS + k / CELL_WORDS] = src[k];
         __syncthreads();
     }
-    for (int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; s < S; s += T) {
+    for (int64_t s = s_first; s < S; s += T) {
         const u64x2 uu = __builtin_nontemporal_load(up + s);
-        Words wr = staged ? lds_words(s_cell, (uint32_t)cell_in(M, uu.x))
-                          : load_words(cells, mzero ? 0 : cell_index(M, uu.x));
+        Words wr = staged ? lds_words(s_cell, (uint32_t)cell_in(M, uu.x)) : load_words(cells, cell_index(M, uu.x));
         const Hit hr = resolve(nodes, wide, cell_of(wr), M, uu.x, n_total);
         // the marginal must have one weight per row distribution 1..D-1
         const int32_t r = hr.i - (int32_t)M.eo;
-        const bool row = !mzero && hr.i >= 0 && 1 + r < D;
+        const bool row = hr.i >= 0 && 1 + r < D;
         const Dist R = dists[row ? 1 + r : 0];
         i32x2 out = {row ? r : -1, -1};
         f64x2 pos = {__builtin_nan(""), __builtin_nan("")};
@@ -663,7 +671,12 @@ __global__ __launch_bounds__(SB_T) __attribute__((amdgpu_waves_per_eu(8))) void 
             pos.x = row ? y : pos.x;
         }
         __builtin_amdgcn_sched_barrier(0);
-        const Hit hc = resolve(nodes, wide, cell_of(wc), R, uu.y, n_total);
+        // The build writes no record for a row without mass: what the
+        // workspace held there must not start a descent, whose nodes (the
+        // collapsed ones are not written either) need not end.
+        Cell cc = cell_of(wc);
+        if (R.flags & DIST_ZERO) cc.aux = -1;
+        const Hit hc = resolve(nodes, wide, cc, R, uu.y, n_total);
         if (row && hc.i >= 0 && !(R.flags & DIST_ZERO)) {
             out.y = hc.i - (int32_t)R.eo;
             if (WANT_X) pos.y = position(R, hc, uu.y);
