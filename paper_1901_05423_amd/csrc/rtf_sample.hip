@@ -662,19 +662,30 @@ __global__ __launch_bounds__(SB_T) __attribute__((amdgpu_waves_per_eu(8))) void 
         i32x2 out = {row ? r : -1, -1};
         f64x2 pos = {__builtin_nan(""), __builtin_nan("")};
         // the column's record is on its way before the row's position is
-        // worked out, and its wait comes after (2^27 pairs of the 4096 x 4096
-        // map: indices 4608 -> 3777 us, with positions 5268 -> 4630)
-        Words wc = load_words(cells, cell_index(R, uu.y));
+        // worked out, and its wait comes after.  With positions the record's
+        // ref and aux are loaded once more, by themselves, past the L2's
+        // retention: 2^27 pairs of the 4096 x 4096 map 4633 -> 4388 us (4485
+        // by an ordinary second load), where indices alone take 3772 us
+        // without it and 4126 with an ordinary one.
+        const int64_t gc = cell_index(R, uu.y);
+        Words wc = load_words(cells, gc);
+        uint64_t ra = 0;
+        if (WANT_X) ra = __builtin_nontemporal_load(reinterpret_cast<const uint64_t *>(&cells[gc].ref));
         __builtin_amdgcn_sched_barrier(0);
         if (WANT_X) {
             const double y = position(M, hr, uu.x);
             pos.x = row ? y : pos.x;
         }
         __builtin_amdgcn_sched_barrier(0);
+        Cell cc = cell_of(wc);
+        if (WANT_X) {
+            asm volatile("" : "+v"(ra));  // kept a load of its own
+            cc.ref = (int32_t)(uint32_t)ra;
+            cc.aux = (int32_t)(uint32_t)(ra >> 32);
+        }
         // The build writes no record for a row without mass: what the
         // workspace held there must not start a descent, whose nodes (the
         // collapsed ones are not written either) need not end.
-        Cell cc = cell_of(wc);
         if (R.flags & DIST_ZERO) cc.aux = -1;
         const Hit hc = resolve(nodes, wide, cc, R, uu.y, n_total);
         if (row && hc.i >= 0 && !(R.flags & DIST_ZERO)) {
