@@ -369,7 +369,8 @@ typedef struct rtf_alias_table {
     uint32_t *status;   /* device: status word */
 } rtf_alias_table;
 
-/* Bytes of workspace for rtf_alias_build; 0 if out of range. */
+/* Bytes of workspace for rtf_alias_build (24 per item, 36 where a table can
+ * exceed the 4096 items whose sums stay on chip); 0 if out of range. */
 size_t rtf_alias_workspace_bytes(int32_t D, int64_t n_total);
 
 /*
@@ -381,8 +382,8 @@ size_t rtf_alias_workspace_bytes(int32_t D, int64_t n_total);
  * One block (for batches of tiny tables, one thread) sets up a distribution:
  * the call suits many small or medium tables (the rows of a 2D map), not one
  * table of millions of items.
- * A distribution with W = 0 is reported by rtf_alias_export as
- * RTF_ERR_ZERO_TOTAL and samples to -1.
+ * A distribution with W = 0, an empty one too, is reported by
+ * rtf_alias_export as RTF_ERR_ZERO_TOTAL and samples to -1.
  */
 rtf_status rtf_alias_build(const uint32_t *w, const int64_t *elem_off, int32_t D,
                            int64_t n_total, void *ws, size_t ws_bytes,

@@ -427,7 +427,7 @@ __global__ __launch_bounds__(AT) void k_alias_sample_2d(const AliasRec *__restri
     int32_t r = -1, c = -1;
     if (Wm != 0) {
         r = alias_pick(recs, 0, eoff[1], Wm, ua);
-        if (r + 1 < D) {  // the marginal must have one item per row table 1..D-1
+        if ((uint32_t)r < (uint32_t)(D - 1)) {  // the marginal must have one item per row table 1..D-1
             const int64_t e0 = eoff[r + 1], n = eoff[r + 2] - e0;
             const uint64_t W = Wd[r + 1];
             c = W == 0 ? -1 : alias_pick(recs, e0, n, W, ub);
@@ -447,9 +447,9 @@ inline size_t a256(size_t x) { return (x + 255) & ~(size_t)255; }
 // of 4096 items 21 and 1819.
 inline bool alias_by_blocks(int32_t D, int64_t n) { return n >= 192 * (int64_t)D || (D <= 1024 && n >= 32 * (int64_t)D); }
 
-// whether one of D distributions, each of at least one item, can hold more
-// than ALDS items
-inline bool alias_may_be_big(int32_t D, int64_t n) { return alias_by_blocks(D, n) && n - (D - 1) > ALDS; }
+// Whether one of the D distributions can hold more than ALDS items, whatever
+// the offsets: empty ones, which break their rule, leave all n to another.
+inline bool alias_may_be_big(int32_t D, int64_t n) { return alias_by_blocks(D, n) && n > ALDS; }
 
 struct AliasLayout {
     size_t status, recs, W, eoff, small_st, large_st, cum, total;
@@ -468,10 +468,9 @@ AliasLayout alias_layout(int32_t D, int64_t n) {
     o = a256(o + sizeof(int64_t) * (size_t)(D + 1));
     L.small_st = o;
     o = a256(o + sizeof(int32_t) * (size_t)n);
-    L.large_st = o;
-    o = a256(o + sizeof(int32_t) * (size_t)n);
-    L.cum = o;
-    if (alias_may_be_big(D, n)) o = a256(o + sizeof(u128) * (size_t)n);  // sums outside LDS
+    // the second stack of the serial form, or the sums outside LDS
+    L.large_st = L.cum = o;
+    o = a256(o + (alias_may_be_big(D, n) ? sizeof(u128) : sizeof(int32_t)) * (size_t)n);
     L.total = o;
     return L;
 }
