@@ -23,13 +23,14 @@ constexpr int QI = 16;
 constexpr int QMAX_LDS_DISTS = 64;  // distributions a k_qmax block sums in LDS
 
 // Index d with off[d] <= i < off[d+1] over off[0..D], found by the whole
-// block (uniform i): each round probes QT evenly spaced offsets at once, so
+// block (uniform i): each round probes NT evenly spaced offsets at once, so
 // 10^4 distributions take two dependent loads instead of a binary search's
 // fourteen.  Every thread of the block must call it.
+template <int NT = QT>
 __device__ inline int32_t block_find_segment(const int64_t *off, int32_t D, int64_t i) {
     int32_t lo = 0, hi = D;  // off[lo] <= i < off[hi]
     while (hi - lo > 1) {
-        const int32_t step = (hi - lo + QT - 1) / QT;
+        const int32_t step = (hi - lo + NT - 1) / NT;
         const int32_t p = lo + ((int32_t)threadIdx.x + 1) * step;
         const int below = (p < hi && off[p] <= i) ? 1 : 0;
         const int32_t nlo = lo + __syncthreads_count(below) * step;
@@ -329,15 +330,25 @@ __device__ inline uint32_t wave_max(uint32_t x) {
     return x;
 }
 
-// Small calls in one launch.  A block of QG threads owns the `per` (1 or 16)
-// distributions from per * blockIdx.x on: with 16, each of its waves one of
-// at most 64 QI weights; every other distribution is the whole block's, one
-// after another.  Up to QI weights per thread stay in registers between the
-// maximum and the quantisation, so that they are read once.
+// Small calls in one launch of blocks of QG threads.  The first ceil(D / per)
+// blocks own `per` distributions each: with 1 the block holds one of at most
+// QG QI weights, with 16 each of its waves one of at most 64 QI, in registers
+// between the maximum and the quantisation, so that the weights are read once.
+// A larger distribution would hold its block up (one block streams 2^15
+// weights in 10 us), so it is left to the blocks after those.  They come in
+// pairs, a pair for each slice of as many elements: only the distributions of
+// its first and of its last element can be larger than the slice.  The first
+// block looks at the one, the second at the other where it is not the same,
+// reads the whole of it for the maximum (2^17 weights in about 5 us) and
+// quantises the slice's part.
 constexpr int QG = 1024;
+template <int PER>
 __global__ __launch_bounds__(QG) void k_qgroup(const float *__restrict__ v, const int64_t *__restrict__ off,
-                                               int32_t D, int64_t n, int per, double *scale,
-                                               uint32_t *__restrict__ out, uint32_t *status) {
+                                               int32_t D, int64_t n, double *scale, uint32_t *__restrict__ out,
+                                               uint32_t *status) {
+    static_assert(PER == 1 || PER == QG / 64, "a distribution per block or per wave");
+    constexpr int OWN = QG / PER;        // threads of a distribution
+    constexpr int64_t HELD = OWN * QI;   // weights they hold, and a slice's elements
     __shared__ uint32_t s_max[QG / 64];
     __shared__ int s_bad;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -350,66 +361,74 @@ __global__ __launch_bounds__(QG) void k_qgroup(const float *__restrict__ v, cons
         e0 = e0 < 0 ? 0 : (e0 > n ? n : e0);
         e1 = e1 < e0 ? e0 : (e1 > n ? n : e1);
     };
-    bool bad = false;
-    if (tid == 0) s_bad = 0;
-    const int32_t d0 = (int32_t)blockIdx.x * per;
-    int64_t e0, e1;
-    if (per > 1 && d0 + w < D) {
-        range(d0 + w, e0, e1);
-        if (e1 - e0 <= 64 * QI) {
-            float xs[QI];
-            uint32_t mx = 0;
-#pragma unroll
-            for (int k = 0; k < QI; ++k) {
-                const int64_t i = e0 + lane + 64 * k;
-                xs[k] = i < e1 ? v[i] : 0.0f;
-            }
-#pragma unroll
-            for (int k = 0; k < QI; ++k) take_max(xs[k], mx, bad);
-            const double s = scale_from_max(__uint_as_float(wave_max(mx)));
-            if (lane == 0) scale[d0 + w] = s;
-#pragma unroll
-            for (int k = 0; k < QI; ++k) {
-                const int64_t i = e0 + lane + 64 * k;
-                if (i < e1) out[i] = quantised(xs[k], s);
-            }
-        }
-    }
-    for (int32_t d = d0; d < d0 + per && d < D; ++d) {
-        range(d, e0, e1);
-        const int64_t cnt = e1 - e0;
-        if (per > 1 && cnt <= 64 * QI) continue;  // a wave's
-        float xs[QI];
-        uint32_t mx = 0;
-        for (int64_t c = e0; c < e1; c += (int64_t)QG * QI) {
-#pragma unroll
-            for (int k = 0; k < QI; ++k) {
-                const int64_t i = c + tid + (int64_t)QG * k;
-                xs[k] = i < e1 ? v[i] : 0.0f;
-            }
-#pragma unroll
-            for (int k = 0; k < QI; ++k) take_max(xs[k], mx, bad);
-        }
+    auto block_max = [&](uint32_t mx) {
         mx = wave_max(mx);
-        __syncthreads();  // the previous distribution's maxima have been read
         if (lane == 0) s_max[w] = mx;
         __syncthreads();
         mx = 0;
         for (int i = 0; i < QG / 64; ++i) mx = s_max[i] > mx ? s_max[i] : mx;
-        const double s = scale_from_max(__uint_as_float(mx));
-        if (tid == 0) scale[d] = s;
-        for (int64_t c = e0; c < e1; c += (int64_t)QG * QI) {
-            if (cnt > (int64_t)QG * QI) {
-#pragma unroll
-                for (int k = 0; k < QI; ++k) {
-                    const int64_t i = c + tid + (int64_t)QG * k;
-                    xs[k] = i < e1 ? v[i] : 0.0f;
-                }
-            }
+        return mx;
+    };
+    bool bad = false;
+    if (tid == 0) s_bad = 0;
+    const int32_t owners = (D + PER - 1) / PER;
+    if ((int32_t)blockIdx.x < owners) {
+        const int32_t d = PER == 1 ? (int32_t)blockIdx.x : (int32_t)blockIdx.x * PER + w;
+        int64_t e0 = 0, e1 = 0;
+        if (d < D) range(d, e0, e1);
+        if (d < D && e1 - e0 <= HELD) {  // (PER == 1: the same in the whole block)
+            const int t = PER == 1 ? tid : lane;
+            float xs[QI];
+            uint32_t mx = 0;
 #pragma unroll
             for (int k = 0; k < QI; ++k) {
-                const int64_t i = c + tid + (int64_t)QG * k;
+                const int64_t i = e0 + t + OWN * k;
+                xs[k] = i < e1 ? v[i] : 0.0f;
+            }
+#pragma unroll
+            for (int k = 0; k < QI; ++k) take_max(xs[k], mx, bad);
+            const double s = scale_from_max(__uint_as_float(PER == 1 ? block_max(mx) : wave_max(mx)));
+            if (t == 0) scale[d] = s;
+#pragma unroll
+            for (int k = 0; k < QI; ++k) {
+                const int64_t i = e0 + t + OWN * k;
                 if (i < e1) out[i] = quantised(xs[k], s);
+            }
+        }
+    } else {
+        const int64_t h = (int64_t)blockIdx.x - owners, a = h / 2 * HELD, b = a + HELD < n ? a + HELD : n;
+        const int32_t d = block_find_segment<QG>(off, D, h & 1 ? b - 1 : a);
+        int64_t e0, e1;
+        range(d, e0, e1);
+        if (e1 - e0 > HELD && (e0 > a || !(h & 1))) {
+            uint32_t mx = 0;
+            // 16-byte loads from the first aligned weight on; an index past
+            // the end is clamped, which a maximum may read twice
+            constexpr int QU = 4;
+            const int64_t lead = (int64_t)((16 - (reinterpret_cast<uintptr_t>(v + e0) & 15)) & 15) / 4;
+            const float4 *v4 = reinterpret_cast<const float4 *>(v + e0 + lead);
+            const int64_t n4 = (e1 - e0 - lead) / 4, tail = e0 + lead + 4 * n4;
+            if (tid < lead) take_max(v[e0 + tid], mx, bad);
+            if (tail + tid < e1) take_max(v[tail + tid], mx, bad);
+            for (int64_t i0 = tid; i0 < n4; i0 += QG * QU) {
+                float4 x[QU];
+#pragma unroll
+                for (int k = 0; k < QU; ++k) x[k] = v4[i0 + QG * k < n4 ? i0 + QG * k : n4 - 1];
+#pragma unroll
+                for (int k = 0; k < QU; ++k) {
+                    take_max(x[k].x, mx, bad);
+                    take_max(x[k].y, mx, bad);
+                    take_max(x[k].z, mx, bad);
+                    take_max(x[k].w, mx, bad);
+                }
+            }
+            const double s = scale_from_max(__uint_as_float(block_max(mx)));
+            if (tid == 0 && e0 >= a) scale[d] = s;  // (and below b, as the element found is)
+            const int64_t q0 = e0 > a ? e0 : a, q1 = e1 < b ? e1 : b;
+#pragma unroll
+            for (int k = 0; k < HELD / QG; ++k) {
+                const int64_t i = q0 + tid + QG * k;
+                if (i < q1) out[i] = quantised(v[i], s);
             }
         }
     }
@@ -421,27 +440,43 @@ __global__ __launch_bounds__(QG) void k_qgroup(const float *__restrict__ v, cons
 }
 
 // The distributions per block of k_qgroup, or 0 for the kernels that cut the
-// weights evenly.  One block streams a distribution at about 10 us per 2^15
-// weights where those take 8 to 13 us in all (a graph's replay, 20 calls): one
-// distribution of 16384 weights 6.7 us against 7.7, of 32768 12.4 against
-// 7.9; 300 of 500 9.1 against 18.0, 16 of 16000 6.8 against 12.5, but two of
-// 100000 34 against 13.  The sizes are not known here, so the totals are held
-// to what a single distribution among them may cost: 2^17 weights, or 2^18
-// where the average of at most 512 sends each wave one (3000 of 10 weights
-// and one of 200000: 68 us against 118).
+// weights evenly.  In us, even cut and k_qgroup (a graph's replay, 20 calls):
+// one distribution of 16384 weights 7.6 and 5.3; 8 of 16000 12.5 and 5.4; 300
+// of 500 18.0 and 6.5; 5000 of 16 to 64 90 and 7.0.  The sizes are not known
+// here, so the totals are held to what the worst of them may cost, a single
+// large distribution that a block reads alone: 2^17 weights, as the even cut
+// takes 12 to 13 for few distributions (8 with one of 130000: 13.1 and 12.2),
+// or 2^18 where the average is at most 512, as it takes longer there (600 with
+// one of 100000 20.8 and 16.3, 512 with one of 260000 73 to 110 and 22.4).
+// From 1025 distributions on a wave each: 3000 of 10 weights and one of 200000
+// 115 and 26.
 int qgroup_per(int32_t D, int64_t n, bool batched) {
     if (!batched || D == 1) return n <= 16384 ? 1 : 0;
-    if (n <= 512 * (int64_t)D) return n <= (1 << 18) ? (D > 1024 ? 16 : 1) : 0;
+    if (n <= 512 * (int64_t)D) return n <= (1 << 18) ? (D > 1024 ? QG / 64 : 1) : 0;
     return n <= (1 << 17) && n <= 16384 * (int64_t)D ? 1 : 0;
+}
+
+template <int PER>
+void launch_qgroup(const float *v, const int64_t *elem_off, int32_t D, int64_t n, uint32_t *out, double *scale,
+                   uint32_t *status, hipStream_t st) {
+    constexpr int64_t HELD = QG / PER * QI;
+    const int64_t slices = n > HELD ? (n + HELD - 1) / HELD : 0;  // else no distribution exceeds what is held
+    hipLaunchKernelGGL(k_qgroup<PER>, dim3((unsigned)((D + PER - 1) / PER + 2 * slices)), dim3(QG), 0, st, v, elem_off, D,
+                       n, scale, out, status);
 }
 
 }  // namespace
 
 hipError_t launch_quantize(const float *v, const int64_t *elem_off, int32_t D, int64_t n_total,
                            uint32_t *out, double *scale, uint32_t *status, hipStream_t st) {
-    if (const int per = qgroup_per(D, n_total, elem_off != nullptr)) {
-        hipLaunchKernelGGL(k_qgroup, dim3((unsigned)((D + per - 1) / per)), dim3(QG), 0, st, v, elem_off, D, n_total,
-                           per, scale, out, status);
+    const int per = qgroup_per(D, n_total, elem_off != nullptr);
+    // weights quantised in place are read by other blocks only in calls of
+    // more than a block or wave holds: those take the even cut, whose maxima
+    // are complete before the first write
+    const bool shared = per && n_total > (int64_t)QG / per * QI;
+    if (per && !(shared && static_cast<const void *>(v) == static_cast<const void *>(out))) {
+        if (per == 1) launch_qgroup<1>(v, elem_off, D, n_total, out, scale, status, st);
+        else launch_qgroup<QG / 64>(v, elem_off, D, n_total, out, scale, status, st);
         return hipGetLastError();
     }
     const int db = (D + 255) / 256;
