@@ -169,10 +169,10 @@ __device__ inline int32_t cell_of_key(uint64_t key, const Dist &P) {
 __device__ inline Leaf make_leaf(uint64_t C, const Dist &P) {
     Leaf L;
     if (C < P.W) {
-        // The form below 2^62 has a multiply and a correction less; the phase
+        // (the form below 2^62 has a multiply and a correction less; the phase
         // is bound by the VALU: 2^24 leaves 170.7 -> 168.3 us, 10,000 tables
-        // 947 -> 936 (four runs each, in turn).
-        L.key = P.s >= 2 ? fixed_point_key_62(C, P.W, P.v, P.s) : fixed_point_key(C, P.W << P.s, P.v, P.s);
+        // 947 -> 936, four runs each, in turn)
+        L.key = fixed_point_key(C, P.W << P.s, P.v, P.s);
         L.cell = cell_of_key(L.key, P);
     } else {
         L.key = ~0ull;
@@ -1691,10 +1691,13 @@ hipError_t launch_balance(Node *nodes, Cell *cells, const Dist *dists, const int
     return hipGetLastError();
 }
 
+// whether whole groups of weights may be read by vector loads
+bool vector_loads(const BuildArgs &a) { return (reinterpret_cast<uintptr_t>(a.w) & 15) == 0; }
+
 template <class T>
 void enqueue_build(const BuildArgs &a, hipStream_t st) {
     constexpr int BT = T::BT;
-    const bool vec = (reinterpret_cast<uintptr_t>(a.w) & 15) == 0;
+    const bool vec = vector_loads(a);
     const dim3 grid((unsigned)a.ntiles);
     const int ts = a.D > 1 ? T::TS_TILES : T::TS_SINGLE;
     const dim3 sumgrid((unsigned)((a.ntiles + ts - 1) / ts));
@@ -1707,10 +1710,6 @@ void enqueue_build(const BuildArgs &a, hipStream_t st) {
             hipLaunchKernelGGL((k_dist_finish<T, true>), dim3((unsigned)((a.D + 255) / 256)), dim3(256), 0, st, a);
         hipLaunchKernelGGL((k_build_tile<T, true, GRID>), grid, dim3(BT), 0, st, a, vec);
         hipLaunchKernelGGL((k_fixup<T, true>), fixgrid, dim3(BT), 0, st, a);
-        return;
-    }
-    if constexpr (T::TILE == TileAlone::TILE && T::BT == TileAlone::BT) {
-        hipLaunchKernelGGL((k_build_tile<T, false, ALONE>), grid, dim3(BT), 0, st, a, vec);
         return;
     }
     hipLaunchKernelGGL((k_tile_sums<T, false>), sumgrid, dim3(BT), 0, st, a, vec);
@@ -1728,7 +1727,8 @@ hipError_t launch_build(const BuildArgs &a, hipStream_t st) {
         BuildArgs one = a;
         one.tile = TileAlone::TILE;
         one.ntiles = 1;
-        enqueue_build<TileAlone>(one, st);
+        hipLaunchKernelGGL((k_build_tile<TileAlone, false, ALONE>), dim3(1), dim3(TileAlone::BT), 0, st, one,
+                           vector_loads(a));
     } else if (a.tile == Tile512::TILE) enqueue_build<Tile512>(a, st);
     else if (a.tile == Tile1024::TILE) enqueue_build<Tile1024>(a, st);
     else enqueue_build<Tile2048>(a, st);
