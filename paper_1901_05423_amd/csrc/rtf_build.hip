@@ -388,11 +388,15 @@ __global__ __launch_bounds__(T::BT) void k_tile_sums(BuildArgs a, bool vec) {
         // but the last), so that every later kernel stays in bounds.
         bool bad = false;
         if (BATCHED) {
+            // (no branch depends on an offset, so that the loads of several
+            // rounds are in flight together)
+#pragma unroll 4
             for (int64_t q = tid; q <= a.D; q += BT) {
+                const int64_t p = q > 0 ? q - 1 : 0;
                 const int64_t e = a.src_elem_off[q], c = a.src_cell_off[q];
-                if (q == 0) bad = bad || e != 0 || c != 0;
-                else bad = bad || e <= a.src_elem_off[q - 1] || c <= a.src_cell_off[q - 1];
-                if (q == a.D) bad = bad || e != a.n_total || c != a.m_total;
+                const int64_t ep = a.src_elem_off[p], cp = a.src_cell_off[p];
+                bad |= q == 0 ? (e != 0) | (c != 0) : (e <= ep) | (c <= cp);
+                bad |= (q == a.D) & ((e != a.n_total) | (c != a.m_total));
             }
         }
         bad = __syncthreads_or(bad);
@@ -401,6 +405,7 @@ __global__ __launch_bounds__(T::BT) void k_tile_sums(BuildArgs a, bool vec) {
             *a.run_count = 0;
             *a.item_count = 0u;
         }
+#pragma unroll 4
         for (int64_t q = tid; q <= a.D; q += BT) {
             const bool own = BATCHED && !bad;
             a.elem_off[q] = own ? a.src_elem_off[q] : (q == a.D ? a.n_total : (BATCHED ? q : 0));
