@@ -15,8 +15,8 @@ constexpr int64_t MAX_I32 = 2147483647;
 
 // Workspace layout of a forest of D distributions, n_total leaves, m_total cells.
 struct Layout {
-    size_t status, nodes, cells, dists, eoff, coff, tsum, tpre, dloc, tdist, dcnt, ditems, runs,
-        total;
+    size_t status, nodes, cells, dists, eoff, coff, tsum, tpre, dloc, tdist, dcnt, icnt, ditems,
+        runs, total;
     int64_t ntiles;
 };
 
@@ -28,9 +28,12 @@ int64_t ntiles_of(int64_t n, int tile) { return (n + tile - 1) / tile; }
 Layout make_layout(int32_t D, int64_t n, int64_t m) {
     Layout L;
     L.ntiles = ntiles_of(n, build_tile(D, n, Tile1024::TILE));
-    const int64_t defer_slots = std::max({ntiles_of(n, Tile512::TILE) * Tile512::DEFER_CAP,
-                                          ntiles_of(n, Tile1024::TILE) * Tile1024::DEFER_CAP,
-                                          ntiles_of(n, Tile2048::TILE) * Tile2048::DEFER_CAP});
+    const auto defer_slots = [n](auto tile) {
+        return DeferLists::slots(ntiles_of(n, tile.TILE), tile.DEFER_CAP, tile.DEFER_MORE);
+    };
+    // (the one-launch form is one tile with as many slots as a Tile2048)
+    int64_t items = std::max(defer_slots(Tile1024()), defer_slots(Tile2048()));
+    if (build_tile(D, n, Tile1024::TILE) == Tile512::TILE) items = std::max(items, defer_slots(Tile512()));
     size_t o = 0;
     L.status = o;
     o = align256(o + 256);
@@ -54,8 +57,10 @@ Layout make_layout(int32_t D, int64_t n, int64_t m) {
     o = align256(o + sizeof(int32_t) * (size_t)(L.ntiles + 2));
     L.dcnt = o;
     o = align256(o + sizeof(int32_t) * (size_t)L.ntiles);
+    L.icnt = o;
+    o = align256(o + sizeof(uint32_t) * (size_t)DeferLists::WORDS);
     L.ditems = o;
-    o = align256(o + sizeof(int32_t) * (size_t)defer_slots);
+    o = align256(o + sizeof(int32_t) * (size_t)items);
     L.runs = o;
     o = align256(o + sizeof(Run) * (size_t)run_cap(m));
     L.total = o;
@@ -123,7 +128,7 @@ rtf_status build_common(const uint32_t *w, const int64_t *elem_off, const int64_
     a.defer_count = reinterpret_cast<int32_t *>(b + L.dcnt);
     a.defer_items = reinterpret_cast<int32_t *>(b + L.ditems);
     a.run_count = reinterpret_cast<uint64_t *>(b + L.status + 64);  // in the status block
-    a.item_count = reinterpret_cast<uint32_t *>(b + L.status + 72);
+    a.item_count = reinterpret_cast<uint32_t *>(b + L.icnt);
     a.runs = reinterpret_cast<Run *>(b + L.runs);
     if (launch_build(a, st) != hipSuccess) return RTF_ERR_HIP;
     *out = f;

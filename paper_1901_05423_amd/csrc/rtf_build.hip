@@ -403,8 +403,8 @@ __global__ __launch_bounds__(T::BT) void k_tile_sums(BuildArgs a, bool vec) {
         if (tid == 0) {
             *a.status = bad ? status_bit(RTF_ERR_INVALID_ARG) : 0u;
             *a.run_count = 0;
-            *a.item_count = 0u;
         }
+        if (tid <= DeferLists::LISTS) a.item_count[tid * DeferLists::STRIDE] = 0u;  // (the last is the flag)
 #pragma unroll 4
         for (int64_t q = tid; q <= a.D; q += BT) {
             const bool own = BATCHED && !bad;
@@ -578,14 +578,14 @@ struct alignas(16) TileSmem {
     int64_t c_begin;
     int32_t win_hi;  // highest window position phase 4 wrote
     int32_t ndefer;
-    int32_t item_base;  // this tile's place in the grid-wide deferral list
-    int32_t items[T::DEFER_CAP];
+    int32_t item_base;  // this tile's place in the grid-wide deferral lists
+    int32_t items[T::DEFER_MORE];
 };
 
 template <class T>
 __device__ inline void push_item(TileSmem<T> &sm, int32_t item) {
     int32_t k = atomicAdd(&sm.ndefer, 1);
-    if (k < T::DEFER_CAP) sm.items[k] = item;
+    if (k < T::DEFER_MORE) sm.items[k] = item;
 }
 
 // the level of local boundary bi: byte bi of the level array (one LDS byte
@@ -891,7 +891,7 @@ __device__ inline void build_keys(const BuildArgs &a, TileSmem<T> &sm, int64_t t
     }
 }
 
-template <class T, bool BATCHED>
+template <class T, bool BATCHED, bool ALONE_TILE>
 __device__ void fixup_body(const BuildArgs &a);
 
 // With 2048-element tiles the LDS allows four blocks per CU.  The
@@ -902,7 +902,7 @@ __device__ void fixup_body(const BuildArgs &a);
 // fits its 80 registers without spills.
 template <class T, bool BATCHED, TileMode MODE>
 __global__ __launch_bounds__(T::BT) __attribute__((amdgpu_waves_per_eu(BATCHED ? T::WAVES_BATCHED : T::WAVES_ONE))) void k_build_tile(BuildArgs a, bool vec) {
-    constexpr int BT = T::BT, TILE = T::TILE, WIN = T::WIN, DEFER_CAP = T::DEFER_CAP;
+    constexpr int BT = T::BT, TILE = T::TILE, WIN = T::WIN, DEFER_CAP = T::DEFER_CAP, DEFER_MORE = T::DEFER_MORE;
     constexpr int LEAF_N = TileSmem<T>::LEAF_N, LVL_N = TileSmem<T>::LVL_N;
     __shared__ TileSmem<T> sm;
     const int tid = threadIdx.x;
@@ -1083,19 +1083,25 @@ __global__ __launch_bounds__(T::BT) __attribute__((amdgpu_waves_per_eu(BATCHED ?
         else if (kind == WIN_TAIL) store_covered(a.cells, c, sm.key[li], KEY_END, g);
         else if (kind != WIN_ALONE) store_covered(a.cells, c, sm.key[li - 1], sm.key[li], g - 1);
     }
-    // the deferred nodes join one grid-wide list (a tile with more than
-    // DEFER_CAP of them is redone whole by the fix-up instead)
+    // the deferred nodes join the grid-wide lists
     const int32_t nd = sm.ndefer;
-    if (tid == 0) a.defer_count[t] = nd;
-    if (nd > 0 && nd <= DEFER_CAP) {  // uniform across the block
-        if (tid == 0) sm.item_base = (int32_t)atomicAdd(a.item_count, (uint32_t)nd);
+    if (tid == 0) {
+        a.defer_count[t] = nd;
+        if (DEFER_MORE > DEFER_CAP && nd > DEFER_MORE) a.item_count[DeferLists::OVER] = 1u;
+    }
+    if (nd > 0 && nd <= DEFER_MORE) {  // uniform across the block
+        if (tid == 0) {
+            const uint32_t k = nd <= DEFER_CAP ? blockIdx.x % DeferLists::SHARED : DeferLists::SHARED;
+            sm.item_base = (int32_t)(k * (uint32_t)DeferLists::shared(a.ntiles, DEFER_CAP) +
+                                     atomicAdd(a.item_count + k * DeferLists::STRIDE, (uint32_t)nd));
+        }
         __syncthreads();
         for (int32_t q = tid; q < nd; q += BT) a.defer_items[sm.item_base + q] = sm.items[q];
     }
     if (MODE == ALONE) {  // the records just stored are read back by this block
         __threadfence();
         __syncthreads();
-        fixup_body<T, false>(a);
+        fixup_body<T, false, true>(a);
     }
 }
 
@@ -1296,15 +1302,15 @@ struct GlobalView {
 template <class T, bool BATCHED>
 __device__ void fixup_tile(const BuildArgs &a, int64_t t);
 
-// The deferred nodes of all tiles are one list: while it is short, each
-// wave of the grid takes one node at a time (its searches then take 64
-// probes per step), else each thread does.  Each block also reads the
-// deferral counts of a contiguous range of tiles in parallel and redoes, one
-// thread per node, a tile that deferred more than it could list.  Then every
+// The deferred nodes of all tiles, their lists taken one after another: while
+// they are few, each wave of the grid takes one node at a time (its searches
+// then take 64 probes per step), else each thread does.  Each block also reads
+// the deferral counts of a contiguous range of tiles in parallel and redoes,
+// one thread per node, a tile that deferred more than are listed.  Then every
 // wave fills an equal share of the cells of the listed guide-table runs.
-template <class T, bool BATCHED>
+template <class T, bool BATCHED, bool ALONE_TILE>
 __device__ void fixup_body(const BuildArgs &a) {
-    constexpr int BT = T::BT, TILE = T::TILE, DEFER_CAP = T::DEFER_CAP;
+    constexpr int BT = T::BT, TILE = T::TILE, DEFER_CAP = T::DEFER_CAP, DEFER_MORE = T::DEFER_MORE;
     constexpr int NW = BT / 64;
     __shared__ int32_t s_list[BT];
     __shared__ int32_t s_nt;
@@ -1314,10 +1320,29 @@ __device__ void fixup_body(const BuildArgs &a) {
         const int64_t tq = j / TILE;  // a listed node belongs to the tile that deferred it
         return a.dists[BATCHED ? find_segment_in(a.elem_off, a.tile_dist[tq], a.tile_dist[tq + 1] + 1, j) : 0];
     };
-    const int64_t ni = *a.item_count;
+    // the lists in use, the last of them (MORE) of tiles that are redone if any is
+    constexpr bool MORE = DEFER_MORE > DEFER_CAP;
+    constexpr int LISTS = ALONE_TILE ? 1 : DeferLists::SHARED + MORE;
+    int32_t end[LISTS];  // the nodes in the lists up to and with each
+#pragma unroll
+    for (int k = 0; k < LISTS; ++k) end[k] = (int32_t)a.item_count[k * DeferLists::STRIDE];
+    const bool over = MORE && a.item_count[DeferLists::OVER] != 0;
+    __builtin_amdgcn_sched_barrier(0);  // all of them in flight together
+#pragma unroll
+    for (int k = 1; k < LISTS; ++k) end[k] = end[k - 1] + (MORE && over && k == LISTS - 1 ? 0 : end[k]);
+    const int32_t listed = over ? DEFER_CAP : DEFER_MORE;
+    const int32_t shared = (int32_t)DeferLists::shared(a.ntiles, DEFER_CAP);
+    auto item = [&](int32_t q) {  // node q of all
+        int32_t at = q;
+#pragma unroll
+        for (int k = 0; k + 1 < LISTS; ++k)
+            if (q >= end[k]) at = (k + 1) * shared + (q - end[k]);
+        return (int64_t)a.defer_items[at];
+    };
+    const int64_t ni = end[LISTS - 1];
     if (ni <= 2 * nwaves) {
         for (int64_t q = gw; q < ni; q += nwaves) {
-            const int64_t j = a.defer_items[q];
+            const int64_t j = item((int32_t)q);
             GlobalView<BATCHED> gv(a, dist_of(j));
             uint64_t kj;
             int32_t c0, c1;
@@ -1329,7 +1354,7 @@ __device__ void fixup_body(const BuildArgs &a) {
         }
     } else {
         for (int64_t q = (int64_t)blockIdx.x * BT + tid; q < ni; q += (int64_t)gridDim.x * BT) {
-            const int64_t j = a.defer_items[q];
+            const int64_t j = item((int32_t)q);
             GlobalView<BATCHED> gv(a, dist_of(j));
             uint64_t kj;
             int32_t c0, c1;
@@ -1344,7 +1369,7 @@ __device__ void fixup_body(const BuildArgs &a) {
         if (tid == 0) s_nt = 0;
         __syncthreads();
         const int64_t t = t0 + tid;
-        if (t < t_hi && a.defer_count[t] > DEFER_CAP) s_list[atomicAdd(&s_nt, 1)] = tid;
+        if (t < t_hi && a.defer_count[t] > listed) s_list[atomicAdd(&s_nt, 1)] = tid;
         __syncthreads();
         const int32_t nt = s_nt;
         for (int32_t q = 0; q < nt; ++q) fixup_tile<T, BATCHED>(a, t0 + s_list[q]);
@@ -1383,7 +1408,7 @@ __device__ void fixup_body(const BuildArgs &a) {
 
 template <class T, bool BATCHED>
 __global__ __launch_bounds__(T::BT) void k_fixup(BuildArgs a) {
-    fixup_body<T, BATCHED>(a);
+    fixup_body<T, BATCHED, false>(a);
 }
 
 template <class T, bool BATCHED>

@@ -33,8 +33,16 @@ struct Tiling {
     // m proportional to n a tile's records fall in about m/n * TILE
     // consecutive cells; records past the window are stored directly.
     static constexpr int WIN = TILE + 128;
-    // Deferred node records kept per tile; more make the fix-up redo the tile.
+    // Deferred node records listed per tile.  A tile with more than DEFER_MORE
+    // makes the fix-up redo it whole, and with it every tile with more than
+    // DEFER_CAP (one pass redoes them all); while there is none, those tiles'
+    // nodes are listed too.  Nodes are deferred at a tile's edges, so small
+    // tiles have no fewer of them (30 distributions of 17475 weights i^20 in
+    // 512-element tiles: the fix-up takes 53 us with room for 32 a tile, 18
+    // with 128; but the runs of 1% non-zero weights, hundreds a tile, 62 us of
+    // build against 90 with 128 listed before the others are redone).
     static constexpr int DEFER_CAP = TILE / 16;
+    static constexpr int DEFER_MORE = DEFER_CAP < 128 && TILE <= 512 ? 128 : DEFER_CAP;
     // Tiles summed per block of the tile-sum pass: a batch's (one wave per
     // search there), and one distribution's (only sums: more bytes per block).
     static constexpr int TS_TILES = BT / 128;
@@ -131,6 +139,25 @@ struct alignas(32) Run {
 // cells and disjoint.
 __host__ __device__ inline int64_t run_cap(int64_t m) { return m / (RUN_CAP + 1) + 1; }
 
+// The deferred nodes are kept in several lists: tile t's in list t mod SHARED,
+// or in the last where it has more than DEFER_CAP of them.  Their lengths lie
+// on lines of their own, since every tile that defers adds to one and adds to
+// one address take 8 ns each (2^20 weights of which one holds 99.9%, 2048
+// tiles: the tile kernel 33.7 us with one list, 21.0 so).
+struct DeferLists {
+    static constexpr int SHARED = 4, LISTS = SHARED + 1, STRIDE = 32;  // counters: 128 bytes apart
+    static constexpr int OVER = LISTS * STRIDE;                        // the flag, after them
+    static constexpr int WORDS = (LISTS + 1) * STRIDE;
+    // slots of a shared list, and of all, for tiles of DEFER_CAP cap and
+    // DEFER_MORE more
+    __host__ __device__ static constexpr int64_t shared(int64_t ntiles, int cap) {
+        return (ntiles + SHARED - 1) / SHARED * cap;
+    }
+    __host__ __device__ static constexpr int64_t slots(int64_t ntiles, int cap, int more) {
+        return SHARED * shared(ntiles, cap) + (more > cap ? ntiles * more : 0);
+    }
+};
+
 // Per-distribution parameters, written by the build's scan kernel.
 struct alignas(64) Dist {
     uint64_t W;   // total weight
@@ -169,8 +196,8 @@ struct BuildArgs {
     uint64_t *tile_prefix;  // [ntiles + 1], the last the grand total
     uint64_t *dist_local;   // [D]: in-tile prefix at each distribution start
     int32_t *defer_count;   // [ntiles]
-    int32_t *defer_items;   // [ntiles * DEFER_CAP]: the deferred nodes of all tiles, one list
-    uint32_t *item_count;   // length of that list
+    int32_t *defer_items;   // the deferred nodes, in lists (DeferLists)
+    uint32_t *item_count;   // the lists' lengths and the flag of a tile beyond them
     int32_t *tile_dist;     // [ntiles + 2]: distribution of element min(t tile, n - 1)
     uint64_t *run_count;    // (runs listed << 32) | cells they cover
     Run *runs;              // [run_cap(m_total)]
