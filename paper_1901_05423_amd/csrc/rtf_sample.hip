@@ -34,8 +34,18 @@ constexpr int STAGE_MIN = 2;    // samples per cell that make staging pay
 // the staged kernel takes 0.6 to 1.05 times the chunk kernel's time, at 2048
 // 0.8 to 1.4, at 512 2.4 to 2.7 (333 uneven tables of 16 to 2048 weights, 186K
 // samples: 85 us staged, 11 us in chunks), since a block then spends its time
-// finding and staging one short segment after another.
+// finding and staging one short segment after another.  Large calls of equal
+// distributions would gain from 2048 on, uneven ones lose, and their totals do
+// not tell them apart (with x and without: 3000 of 250 cells and 2796 samples
+// 68 and 44 us staged, 86 and 70 in chunks; 1000 of 16 to 4096 weights, 176
+// cells and 2097 samples on average, 52 and 35 against 32 and 25).
 constexpr int64_t STAGE_SEGMENT = 4096;
+
+// One distribution of a batched call is staged from so many samples on, with x
+// and without: 1000 cells, 2^22 samples 33.6 and 22.5 us by the plain kernel's
+// quads, 24.1 and 15.4 staged; 2^24 144 and 103, 78 and 44; 2^20 7.6 and 5.8,
+// 9.9 and 6.2.
+constexpr int64_t STAGE_ONE_X = 1 << 22, STAGE_ONE = 1 << 21;
 
 // Bytes of guide table up to which single-distribution sampling fetches the
 // records by whole quads of lanes.  While the table fits the L2s the texture
@@ -764,11 +774,10 @@ hipError_t launch_sample(const Node *nodes, const Wide *wide, const Cell *cells,
                          const int64_t *sample_off, int32_t D, int64_t n_total, int64_t m_total,
                          const uint64_t *u, int64_t S, int32_t *idx, double *x,
                          hipStream_t st) {
-    const bool batched = sample_off != nullptr && D > 1;  // one distribution's samples are all its own
     // many samples per cell and per distribution, and small distributions:
     // stage the cells in LDS (two blocks of SB_T threads per CU)
-    if (batched && S >= (int64_t)STAGE_MIN * m_total && S >= STAGE_SEGMENT * D &&
-        m_total <= (int64_t)LCELLS * D) {
+    const bool enough = D == 1 ? S >= (x ? STAGE_ONE_X : STAGE_ONE) : S >= STAGE_SEGMENT * D;
+    if (sample_off && enough && S >= (int64_t)STAGE_MIN * m_total && m_total <= (int64_t)LCELLS * D) {
         int64_t nb = (S + 4 * SB_T - 1) / (4 * SB_T);
         nb = nb < 512 ? nb : 512;
         if (x)
@@ -779,6 +788,7 @@ hipError_t launch_sample(const Node *nodes, const Wide *wide, const Cell *cells,
                                dists, sample_off, D, n_total, u, S, idx, x);
         return hipGetLastError();
     }
+    const bool batched = sample_off != nullptr && D > 1;  // one distribution's samples are all its own
     const int64_t chunk = S >= CHUNK_LONG ? 2048 : 512;
     const dim3 g(batched ? grid_for((S + chunk / 256 - 1) / (chunk / 256)) : grid_for(S)), b(256);
     auto go = [&](auto kernel) {
