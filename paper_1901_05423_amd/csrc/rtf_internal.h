@@ -279,6 +279,14 @@ __host__ __device__ inline uint64_t fixed_point_key(uint64_t C, uint64_t d, uint
     return q1 + (r != 0 ? 1 : 0);
 }
 
+// Whether a search at reference jn of a forest of nt nodes reads another one
+// after `steps` of them: a reference outside the forest, or a path longer than
+// it, can only come from a damaged workspace.  (nt may be the largest int32,
+// which an int32 count would never pass.)
+__host__ __device__ inline bool descent_goes_on(int32_t jn, uint32_t steps, int32_t nt) {
+    return jn >= 0 && jn < nt && steps <= (uint32_t)nt;
+}
+
 // Level of the boundary between two neighbouring leaves: 64 - clz(a ^ b).
 __host__ __device__ inline int level_of(uint64_t a, uint64_t b) { return 64 - clz64(a ^ b); }
 

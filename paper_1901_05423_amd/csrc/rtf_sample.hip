@@ -334,15 +334,16 @@ __device__ inline Hit resolve(const Node *nodes, const Wide *wide, const Cell &c
         // U_{i+1} read after the descent.
         const int32_t nt = (int32_t)n_total;
         uint64_t klo = c.k[CELL_KEYS - 1], khi = 0;
-        int32_t jn = c.aux, steps = 0;
+        int32_t jn = c.aux;
+        uint32_t steps = 0;
         if (wide) {
             // collapsed nodes: two binary levels per record (Sec. 5)
-            while (jn >= 0 && jn < nt && steps <= nt) {
+            while (descent_goes_on(jn, steps, nt)) {
                 step_wide(load_wide(wide, jn), u, jn, klo, khi);
                 ++steps;
             }
         } else {
-            while (jn >= 0 && jn < nt && steps <= nt) {
+            while (descent_goes_on(jn, steps, nt)) {
                 const Node nd = load_node(nodes, jn);
                 step_node(nd.key, nd.c0, nd.c1, u, jn, klo, khi);
                 ++steps;
