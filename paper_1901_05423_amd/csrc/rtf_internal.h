@@ -245,11 +245,12 @@ __host__ __device__ inline uint64_t reciprocal_2by1(uint64_t d) {
 
 // Key U = ceil(C * 2^64 / W) for 0 <= C < W < 2^62, given s = clz(W) and
 // v = reciprocal_2by1(W << s).  q = floor(u1 (2^64 + v) / 2^64), u1 = C << s,
-// is the quotient's floor or one below it, since 2^64 + v falls short of
-// 2^128 / (W << s) by less than one.  The remainder C 2^64 - q W then lies in
-// [0, 2 W), below 2^63, so its low word p' = -(q W) is all of it, and U is q
-// plus one where p' is not 0, plus another where p' > W, that is where
-// p = q W (its low word) is below 2^64 - W.
+// is the quotient's floor or one below it: 2^64 + v falls short of
+// 2^128 / (W << s) by at most one (exactly one where W is a power of two), and
+// u1 < 2^64, so q exceeds the exact quotient minus two.  The remainder
+// C 2^64 - q W then lies in [0, 2 W), below 2^63, so its low word p' = -(q W)
+// is all of it, and U is q plus one where p' is not 0, plus another where
+// p' > W, that is where p = q W (its low word) is below 2^64 - W.
 __host__ __device__ inline uint64_t fixed_point_key_62(uint64_t C, uint64_t W, uint64_t v, uint32_t s) {
     const uint64_t u1 = C << s;
     const uint64_t q = u1 + mulhi64(v, u1);
@@ -277,6 +278,22 @@ __host__ __device__ inline uint64_t fixed_point_key(uint64_t C, uint64_t d, uint
         r -= d;
     }
     return q1 + (r != 0 ? 1 : 0);
+}
+
+// The weight, in FP64, of an interval with keys lo and hi (KEY_END: the
+// distribution's end) and partial sum Ci = floor(lo W / 2^64), given s =
+// clz(W).  Below W = 2^61 it needs no second product of 64-bit words:
+// (hi - lo) W / 2^64 differs from it by less than W 2^-63 (KEY_END stands one
+// below 2^64) and its FP64 value by 2^-20 more, so rounding that to an integer
+// gives the weight exactly.
+__host__ __device__ inline double interval_weight(uint64_t lo, uint64_t hi, uint64_t Ci, uint64_t W, uint32_t s) {
+    if (s >= 3) {
+        const uint64_t d = hi - lo;
+        return __builtin_rint(__builtin_fma((double)(uint32_t)(d >> 32), 0x1p32, (double)(uint32_t)d) *
+                              (__builtin_fma((double)(uint32_t)(W >> 32), 0x1p32, (double)(uint32_t)W) * 0x1p-64));
+    }
+    const uint64_t Cn = (hi == KEY_END) ? W : mulhi64(hi, W);
+    return (double)(uint32_t)(Cn - Ci);
 }
 
 // Whether a search at reference jn of a forest of nt nodes reads another one

@@ -369,27 +369,16 @@ __device__ inline Hit descend(const Node *nodes, const Wide *wide, const Cell *c
 // C_i = floor(U_i * W / 2^64) recovers the exact partial sum from a key.
 // For the sampled i, 0 <= t - C_i < w_i = C_{i+1} - C_i < 2^32 and
 // i - eo < 2^31, so those convert to FP64 from 32 bits (one instruction
-// each, and the same values).  The weight itself needs no second product:
-// (U_{i+1} - U_i) W / 2^64 differs from w_i by less than W 2^-63 (KEY_END
-// stands one below 2^64) and its FP64 value by 2^-20 more, so for W < 2^61
-// rounding it to an integer gives w_i exactly.  The division by n is a
-// product with 1/n, computed once where the distribution is the same for a
-// whole loop; the result is kept at most 1 (it could round one ulp above 1
-// when the offset in the interval rounds up to w_i in the last leaf).
+// each, and the same values).  The division by n is a product with 1/n,
+// computed once where the distribution is the same for a whole loop; the
+// result is kept at most 1 (it could round one ulp above 1 when the offset in
+// the interval rounds up to w_i in the last leaf).
 __device__ inline double position(const Dist &P, const Hit &h, uint64_t u) {
     const uint64_t W = P.W;
     const uint64_t Ci = mulhi64(h.lo, W);
     const uint64_t t = mulhi64(u, W);
     const uint64_t lo = u * W;
-    double w;
-    if (P.s >= 3) {  // W < 2^61
-        const uint64_t d = h.hi - h.lo;
-        w = __builtin_rint(__builtin_fma((double)(uint32_t)(d >> 32), 0x1p32, (double)(uint32_t)d) *
-                           (__builtin_fma((double)(uint32_t)(W >> 32), 0x1p32, (double)(uint32_t)W) * 0x1p-64));
-    } else {
-        const uint64_t Cn = (h.hi == KEY_END) ? W : mulhi64(h.hi, W);
-        w = (double)(uint32_t)(Cn - Ci);
-    }
+    const double w = interval_weight(h.lo, h.hi, Ci, W, P.s);
     const double lod = __builtin_fma((double)(uint32_t)(lo >> 32), 0x1p32, (double)(uint32_t)lo);
     const double frac = div_small(__builtin_fma(lod, 0x1p-64, (double)(uint32_t)(t - Ci)), w);
     const double x = ((double)(h.i - (int32_t)P.eo) + frac) * (1.0 / (double)P.n);
