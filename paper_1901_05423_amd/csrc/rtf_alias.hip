@@ -94,12 +94,13 @@ __global__ __launch_bounds__(64) void k_alias_serial(const uint32_t *__restrict_
 // those of at most ALDS items, whose lists stay in LDS with 64-bit running
 // sums (below n W <= 2^56 there), k_alias_big larger ones, with lists and
 // 128-bit sums in the workspace, in rounds of ABT items.  A block is a chain
-// of scans and LDS searches, so it is sized for three blocks a CU (41 KB, 80
-// registers) and a thread advances AQ searches together.  4097 tables of a
-// 4096 x 4096 map (67 MB read, 268 MB written, 65 us at the copy rate): 4712
-// us by one thread a table, 180 us by blocks; 1024 threads a block 474 us;
-// eight searches together at two blocks a CU 157 us, but 30,000 tables of 300
-// items then take 531 us against 341.
+// of scans and LDS searches, so it is sized for three blocks a CU: 41 KB, and
+// 80 registers, to which it is held at the price of 44 spilled bytes a thread.
+// A thread advances AQ searches together.  4097 tables of a 4096 x 4096 map
+// (67 MB read, 268 MB written, 65 us at the copy rate): 4712 us by one thread
+// a table, 180 us by blocks; at two blocks a CU, where nothing spills, 175 us
+// with four searches together and 157 with eight, but 30,000 tables of 300
+// items then take 531 us against 341; 1024 threads a block 474 us.
 constexpr int ABT = 512;
 constexpr int ALDS = 4096;
 constexpr int AIT = ALDS / ABT;
